@@ -39,14 +39,17 @@ namespace fb {
 template <typename T, int D, int MR, int NW, int OCC, int NSTAGE>
 __global__ __launch_bounds__(NW * 64, OCC) void attn_fwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
-    T* __restrict__ O, float* __restrict__ L, int N, int nRB, int total, float scale, int causal, int grp) {
+    T* __restrict__ O, float* __restrict__ L, int N, int nRB, int total, float scale, int causal, int resident, int grp) {
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BR = 16 * MR * NW;
   __shared__ __attribute__((aligned(16))) T lds[NSTAGE][2 * G::kTileElems];
 
   int bh, rb;
-  map_block(nRB, total, bh, rb, causal != 0);
+  if (resident > 0)
+    map_block_causal(nRB, total, resident, true, bh, rb);
+  else
+    map_block(nRB, total, bh, rb, causal != 0);
   const int64_t hoff = (int64_t)bh * N * D;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
   const int l = lane_id(), g = l >> 4, j = l & 15;
@@ -179,14 +182,17 @@ template <typename T, int D, int MR, int NW, int OCC, int NSTAGE>
 __global__ __launch_bounds__(NW * 64, OCC) void attn_bwd_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ L,
-    T* __restrict__ dQ, float* __restrict__ Dout, int N, int nRB, int total, float scale, int causal, int grp) {
+    T* __restrict__ dQ, float* __restrict__ Dout, int N, int nRB, int total, float scale, int causal, int resident, int grp) {
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BR = 16 * MR * NW;
   __shared__ __attribute__((aligned(16))) T lds[NSTAGE][2 * G::kTileElems];
 
   int bh, rb;
-  map_block(nRB, total, bh, rb, causal != 0);
+  if (resident > 0)
+    map_block_causal(nRB, total, resident, true, bh, rb);
+  else
+    map_block(nRB, total, bh, rb, causal != 0);
   const int64_t hoff = (int64_t)bh * N * D;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
   const int l = lane_id(), g = l >> 4, j = l & 15;
@@ -303,7 +309,7 @@ template <typename T, int D, int MC, int NW, int OCC, int NSTAGE, bool kGQA, int
 __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Dv,
-    T* __restrict__ dK, T* __restrict__ dV, int N, int nRB, int total, float scale, int causal, int grp,
+    T* __restrict__ dK, T* __restrict__ dV, int N, int nRB, int total, float scale, int causal, int resident, int grp,
     float* __restrict__ parts_out = nullptr, int nparts = 1, int flush_tiles = 0) {
   static_assert(KS == 1 || KS == 2, "wave sets");
   using E = Elt<T>;
@@ -337,6 +343,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
   int bh, rb, part = 0;
   if constexpr (kParts)
     map_column_job(nRB, total, nparts, bh, rb, part);
+  else if (resident > 0)
+    map_block_causal(nRB, total, resident, false, bh, rb);
   else
     map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
@@ -551,7 +559,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
     const T* __restrict__ UK, const T* __restrict__ UV, const float* __restrict__ L,
     const float* __restrict__ Dv, const T* __restrict__ dQ, const float* __restrict__ alpha_in,
     T* __restrict__ Qt, T* __restrict__ dOt, float* __restrict__ alpha_out, float* __restrict__ E_out,
-    int N, int nRB, int total, float scale, int causal, int grp) {
+    int N, int nRB, int total, float scale, int causal, int resident, int grp) {
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr bool kDQ = kForm == kWithDQ;
@@ -560,7 +568,10 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
   __shared__ __attribute__((aligned(16))) T lds[NSTAGE][4 * G::kTileElems];
 
   int bh, rb;
-  map_block(nRB, total, bh, rb, causal != 0);
+  if (resident > 0)
+    map_block_causal(nRB, total, resident, true, bh, rb);
+  else
+    map_block(nRB, total, bh, rb, causal != 0);
   const int64_t hoff = (int64_t)bh * N * D;
   const int64_t soff = (int64_t)bh * N;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
@@ -810,14 +821,17 @@ template <typename T, int D, int MR, int NW, int OCC, int NSTAGE>
 __global__ __launch_bounds__(NW * 64, OCC) void bob3_alpha_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ UQ,
     const T* __restrict__ UK, const float* __restrict__ L, float* __restrict__ alpha_out, int N, int nRB,
-    int total, float scale, int causal, int grp) {
+    int total, float scale, int causal, int resident, int grp) {
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BR = 16 * MR * NW;
   __shared__ __attribute__((aligned(16))) T lds[NSTAGE][2 * G::kTileElems];
 
   int bh, rb;
-  map_block(nRB, total, bh, rb, causal != 0);
+  if (resident > 0)
+    map_block_causal(nRB, total, resident, true, bh, rb);
+  else
+    map_block(nRB, total, bh, rb, causal != 0);
   const int64_t hoff = (int64_t)bh * N * D;
   const int64_t soff = (int64_t)bh * N;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
@@ -909,7 +923,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
     const T* __restrict__ dO, const T* __restrict__ UQ, const T* __restrict__ UK,
     const T* __restrict__ UV, const float* __restrict__ L, const float* __restrict__ Dv,
     const float* __restrict__ alpha_in, const float* __restrict__ E_in,
-    T* __restrict__ Kt, T* __restrict__ Vt, int N, int nRB, int total, float scale, int causal, int grp,
+    T* __restrict__ Kt, T* __restrict__ Vt, int N, int nRB, int total, float scale, int causal, int resident, int grp,
     float* __restrict__ parts_out = nullptr, int nparts = 1, int flush_tiles = 0) {
   static_assert(KS == 1 || KS == 2, "wave sets");
   using E = Elt<T>;
@@ -935,6 +949,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
   int bh, rb, part = 0;
   if constexpr (kParts)
     map_column_job(nRB, total, nparts, bh, rb, part);
+  else if (resident > 0)
+    map_block_causal(nRB, total, resident, false, bh, rb);
   else
     map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
@@ -1177,7 +1193,7 @@ __global__ __launch_bounds__(2 * NP * 64, 2) void bob_pass2_pair_kernel(
     const T* __restrict__ dO, const T* __restrict__ UQ, const T* __restrict__ UK,
     const T* __restrict__ UV, const float* __restrict__ L, const float* __restrict__ Dv,
     const float* __restrict__ alpha_in, const float* __restrict__ E_in,
-    T* __restrict__ Kt, T* __restrict__ Vt, int N, int nRB, int total, float scale, int causal, int grp) {
+    T* __restrict__ Kt, T* __restrict__ Vt, int N, int nRB, int total, float scale, int causal, int resident, int grp) {
   static_assert(sizeof(T) == 2, "bf16 only");
   using E = Elt<T>;
   using G = Geo<T, D>;
@@ -1195,7 +1211,10 @@ __global__ __launch_bounds__(2 * NP * 64, 2) void bob_pass2_pair_kernel(
   __shared__ __attribute__((aligned(16))) SmemPair sm;
 
   int bh, rb;
-  map_block(nRB, total, bh, rb);
+  if (resident > 0)
+    map_block_causal(nRB, total, resident, false, bh, rb);
+  else
+    map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
   const int l = lane_id(), g = l >> 4, j = l & 15;
   const int w = wave_id();

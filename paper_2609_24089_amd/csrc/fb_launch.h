@@ -146,6 +146,33 @@ inline Grid grid_for(const Problem& p, int rows_per_block, bool kv_heads = false
   return g;
 }
 
+// Workgroups of kKernel that fit one CU (1 if the runtime cannot tell), read
+// once per kernel: a property of its code object.
+template <auto kKernel> int resident_blocks(int threads) {
+  static const int resident = [&] {
+    int n = 0;
+    const hipError_t rc = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)kKernel, threads, 0);
+    return rc == hipSuccess && n > 0 ? n : 1;
+  }();
+  return resident;
+}
+
+// The `resident` argument of a kernel launch: the workgroups of kKernel that
+// fit one CU if the causal grid is to run in the balanced order
+// (map_block_causal), else 0 (heads one after another).  A grid of one round
+// has a CU for every block, and on grids of more than about six times the
+// resident blocks the refills balance the load by themselves while blocks of
+// one head in flight at a time share its streamed tiles in L2: measured bf16
+// B4 H12 N16384 d64 (24 and 48 rounds, 4 and 3 resident), the balanced order ran
+// Pass 1 5% and Pass 2 3% slower and the forward 2% faster; at N4096 (6 and 12
+// rounds) it ran Pass 1 6%, Pass 2 15% and the forward 24% faster.
+template <auto kKernel> int causal_resident(const Problem& p, const Grid& g, int threads) {
+  constexpr int kCUs = kXCDs * kCUsPerXCD;
+  if (p.causal == 0 || g.total <= kCUs) return 0;
+  const int resident = resident_blocks<kKernel>(threads);
+  return g.total <= (int64_t)6 * kCUs * resident ? resident : 0;
+}
+
 // ---------------------------------------------------------------------------
 // Column kernels (the first backward's dK, dV and Pass 2's Kt, Vt): how one
 // problem's column blocks are laid out over workgroups.
@@ -287,9 +314,11 @@ int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V
                    hipStream_t s) {
   constexpr Shape c = Cfg<T, D>::kFwd;
   const Grid g = grid_for(p, 16 * c.mr * c.nw);
+  constexpr auto kernel = &attn_fwd_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
+  const int res = causal_resident<kernel>(p, g, 64 * c.nw);
   (void)hipGetLastError();
-  hipLaunchKernelGGL((attn_fwd_kernel<T, D, c.mr, c.nw, c.occ, c.st>), dim3(g.total), dim3(64 * c.nw), 0, s,
-                     (const T*)Q, (const T*)K, (const T*)V, (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, group(p));
+  hipLaunchKernelGGL(kernel, dim3(g.total), dim3(64 * c.nw), 0, s,
+                     (const T*)Q, (const T*)K, (const T*)V, (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
   return finish_launch();
 }
 
@@ -308,7 +337,7 @@ int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const vo
       hipLaunchKernelGGL((attn_bwd_cols_kernel<T, D, cc.mr, cc.nw, cc.occ, cc.st, true, 1, true, kF, cc.kl != 0>),
                          dim3(gc.total * cp.parts), dim3(64 * cc.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                          (const T*)dO, L, Dv, (T*)dK, (T*)dV, (int)p.N, gc.nRB, gc.total, p.scale, p.causal,
-                         group(p), parts_ws, cp.parts, cp.flush_tiles);
+                         0, group(p), parts_ws, cp.parts, cp.flush_tiles);
       const int64_t plane = p.B * p.Hkv * p.N * p.d;
       const int blocks = (int)std::min<int64_t>((plane / 2 + 255) / 256, 4096);
       hipLaunchKernelGGL((bob_column_parts_reduce_kernel<T>), dim3(blocks), dim3(256), 0, s, (const float*)parts_ws,
@@ -316,11 +345,13 @@ int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const vo
       return finish_launch();
     }
     auto cols = [&](auto gqa, auto ks) {
-      hipLaunchKernelGGL((attn_bwd_cols_kernel<T, D, cc.mr, cc.nw, cc.occ, cc.st, decltype(gqa)::value,
-                                               decltype(ks)::value, false, kF, cc.kl != 0>),
-                         dim3(gc.total), dim3(64 * cc.nw * decltype(ks)::value), 0, s, (const T*)Q, (const T*)K,
+      constexpr auto kernel = &attn_bwd_cols_kernel<T, D, cc.mr, cc.nw, cc.occ, cc.st, decltype(gqa)::value,
+                                                    decltype(ks)::value, false, kF, cc.kl != 0>;
+      const int res = causal_resident<kernel>(p, gc, 64 * cc.nw * decltype(ks)::value);
+      (void)hipGetLastError();
+      hipLaunchKernelGGL(kernel, dim3(gc.total), dim3(64 * cc.nw * decltype(ks)::value), 0, s, (const T*)Q, (const T*)K,
                          (const T*)V, (const T*)dO, L, Dv, (T*)dK, (T*)dV, (int)p.N, gc.nRB, gc.total, p.scale,
-                         p.causal, group(p), (float*)nullptr, 1, cp.flush_tiles);
+                         p.causal, res, group(p), (float*)nullptr, 1, cp.flush_tiles);
     };
     const bool gqa = group(p) != 1;
     if constexpr (ColumnShape<T, D, false, kF>::kTwoFit) {
@@ -345,10 +376,12 @@ int32_t launch_bwd(const Problem& p, const void* Q, const void* K, const void* V
                    hipStream_t s, const ColumnPlan& cp, float* parts_ws) {
   constexpr Shape cr = Cfg<T, D>::kRows;
   const Grid gr = grid_for(p, 16 * cr.mr * cr.nw);
+  constexpr auto rows = &attn_bwd_rows_kernel<T, D, cr.mr, cr.nw, cr.occ, cr.st>;
+  const int res = causal_resident<rows>(p, gr, 64 * cr.nw);
   (void)hipGetLastError();
-  hipLaunchKernelGGL((attn_bwd_rows_kernel<T, D, cr.mr, cr.nw, cr.occ, cr.st>), dim3(gr.total), dim3(64 * cr.nw), 0, s,
+  hipLaunchKernelGGL(rows, dim3(gr.total), dim3(64 * cr.nw), 0, s,
                      (const T*)Q, (const T*)K, (const T*)V, (const T*)O, (const T*)dO, L, (T*)dQ, Dv,
-                     (int)p.N, gr.nRB, gr.total, p.scale, p.causal, group(p));
+                     (int)p.N, gr.nRB, gr.total, p.scale, p.causal, res, group(p));
   int32_t rc = finish_launch();
   if (rc != BOB_OK) return rc;
   if (cp.flush_tiles > 0)
@@ -362,23 +395,26 @@ int32_t launch_pass1(const Problem& p, const void* Q, const void* K, const void*
                      const void* dO, const void* UQ, const void* UK, const void* UV, const float* L,
                      const float* Dv, const void* dQ, void* Qt, void* dOt, float* alpha, float* E,
                      hipStream_t s) {
-  (void)hipGetLastError();
   if (dQ != nullptr) {
     constexpr Shape c = Cfg<T, D>::kP1;
     const Grid g = grid_for(p, 16 * c.mr * c.nw);
-    hipLaunchKernelGGL((bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kWithDQ, c.ds, c.pf>), dim3(g.total, c.ds),
-                       dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)O,
+    constexpr auto kernel = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kWithDQ, c.ds, c.pf>;
+    const int res = causal_resident<kernel>(p, g, 64 * c.nw);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kernel, dim3(g.total, c.ds), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)O,
                        (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, (const T*)dQ,
                        (const float*)nullptr, (T*)Qt, (T*)dOt, alpha, E, (int)p.N, g.nRB, g.total, p.scale,
-                       p.causal, group(p));
+                       p.causal, res, group(p));
   } else {
     constexpr Shape c = Cfg<T, D>::kP1Six;
     const Grid g = grid_for(p, 16 * c.mr * c.nw);
-    hipLaunchKernelGGL((bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kSixAcc, c.ds, c.pf>), dim3(g.total, c.ds),
-                       dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)O,
+    constexpr auto kernel = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kSixAcc, c.ds, c.pf>;
+    const int res = causal_resident<kernel>(p, g, 64 * c.nw);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kernel, dim3(g.total, c.ds), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)O,
                        (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, (const T*)nullptr,
                        (const float*)nullptr, (T*)Qt, (T*)dOt, alpha, E, (int)p.N, g.nRB, g.total, p.scale,
-                       p.causal, group(p));
+                       p.causal, res, group(p));
   }
   return finish_launch();
 }
@@ -389,10 +425,12 @@ int32_t launch_alpha3(const Problem& p, const void* Q, const void* K, const void
                       const float* L, float* alpha, hipStream_t s) {
   constexpr Shape c = Cfg<T, D>::kAlpha;
   const Grid g = grid_for(p, 16 * c.mr * c.nw);
+  constexpr auto kernel = &bob3_alpha_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
+  const int res = causal_resident<kernel>(p, g, 64 * c.nw);
   (void)hipGetLastError();
-  hipLaunchKernelGGL((bob3_alpha_kernel<T, D, c.mr, c.nw, c.occ, c.st>), dim3(g.total), dim3(64 * c.nw), 0, s,
+  hipLaunchKernelGGL(kernel, dim3(g.total), dim3(64 * c.nw), 0, s,
                      (const T*)Q, (const T*)K, (const T*)UQ, (const T*)UK, L, alpha, (int)p.N, g.nRB, g.total,
-                     p.scale, p.causal, group(p));
+                     p.scale, p.causal, res, group(p));
   return finish_launch();
 }
 
@@ -402,11 +440,12 @@ int32_t launch_rows3(const Problem& p, const void* Q, const void* K, const void*
                      const float* alpha, void* Qt, void* dOt, float* E, hipStream_t s) {
   constexpr Shape c = Cfg<T, D>::kP1;
   const Grid g = grid_for(p, 16 * c.mr * c.nw);
+  constexpr auto kernel = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kAlphaGiven, c.ds, c.pf>;
+  const int res = causal_resident<kernel>(p, g, 64 * c.nw);
   (void)hipGetLastError();
-  hipLaunchKernelGGL((bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kAlphaGiven, c.ds, c.pf>), dim3(g.total, c.ds),
-                     dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)nullptr,
+  hipLaunchKernelGGL(kernel, dim3(g.total, c.ds), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)nullptr,
                      (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, (const T*)nullptr, alpha,
-                     (T*)Qt, (T*)dOt, (float*)nullptr, E, (int)p.N, g.nRB, g.total, p.scale, p.causal, group(p));
+                     (T*)Qt, (T*)dOt, (float*)nullptr, E, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
   return finish_launch();
 }
 
@@ -426,7 +465,7 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
       hipLaunchKernelGGL((bob_pass2_kernel<T, D, c.mr, c.nw, c.occ, c.st, true, 1, c.pf != 0, true, kF>),
                          dim3(g.total * cp.parts), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                          (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt,
-                         (int)p.N, g.nRB, g.total, p.scale, p.causal, group(p), parts_ws, cp.parts,
+                         (int)p.N, g.nRB, g.total, p.scale, p.causal, 0, group(p), parts_ws, cp.parts,
                          cp.flush_tiles);
       const int64_t plane = p.B * p.Hkv * p.N * p.d;
       const int blocks = (int)std::min<int64_t>((plane / 2 + 255) / 256, 4096);
@@ -441,7 +480,7 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
         hipLaunchKernelGGL((bob_pass2_kernel<T, D, w.mr, w.nw, w.occ, w.st, decltype(kv)::value, 1, w.pf != 0>),
                            dim3(g.total), dim3(64 * w.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)dO,
                            (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt, (int)p.N,
-                           g.nRB, g.total, p.scale, p.causal, group(p), (float*)nullptr, 1, 0);
+                           g.nRB, g.total, p.scale, p.causal, 0, group(p), (float*)nullptr, 1, 0);
       };
       if (cp.wide) {
         gqa ? wide(std::true_type{}) : wide(std::false_type{});
@@ -451,10 +490,12 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
     if constexpr (!kF && Cfg<T, D>::kP2P.mr > 0) {
       constexpr Shape q = Cfg<T, D>::kP2P;
       auto pairs = [&](auto kv) {
-        hipLaunchKernelGGL((bob_pass2_pair_kernel<T, D, q.nw / 2, decltype(kv)::value>), dim3(g.total),
-                           dim3(64 * q.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)dO,
+        constexpr auto kernel = &bob_pass2_pair_kernel<T, D, q.nw / 2, decltype(kv)::value>;
+        const int res = causal_resident<kernel>(p, g, 64 * q.nw);
+        (void)hipGetLastError();
+        hipLaunchKernelGGL(kernel, dim3(g.total), dim3(64 * q.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)dO,
                            (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt, (int)p.N,
-                           g.nRB, g.total, p.scale, p.causal, group(p));
+                           g.nRB, g.total, p.scale, p.causal, res, group(p));
       };
       if (cp.pairs) {
         gqa ? pairs(std::true_type{}) : pairs(std::false_type{});
@@ -462,11 +503,13 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
       }
     }
     auto pass2 = [&](auto gqa, auto ks) {
-      hipLaunchKernelGGL((bob_pass2_kernel<T, D, c.mr, c.nw, c.occ, c.st, decltype(gqa)::value, decltype(ks)::value,
-                                           c.pf != 0, false, kF>),
-                         dim3(g.total), dim3(64 * c.nw * decltype(ks)::value), 0, s, (const T*)Q, (const T*)K,
+      constexpr auto kernel = &bob_pass2_kernel<T, D, c.mr, c.nw, c.occ, c.st, decltype(gqa)::value,
+                                                decltype(ks)::value, c.pf != 0, false, kF>;
+      const int res = causal_resident<kernel>(p, g, 64 * c.nw * decltype(ks)::value);
+      (void)hipGetLastError();
+      hipLaunchKernelGGL(kernel, dim3(g.total), dim3(64 * c.nw * decltype(ks)::value), 0, s, (const T*)Q, (const T*)K,
                          (const T*)V, (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E,
-                         (T*)Kt, (T*)Vt, (int)p.N, g.nRB, g.total, p.scale, p.causal, group(p), (float*)nullptr, 1,
+                         (T*)Kt, (T*)Vt, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p), (float*)nullptr, 1,
                          cp.flush_tiles);
     };
     if constexpr (ColumnShape<T, D, true, kF>::kTwoFit) {
