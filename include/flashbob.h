@@ -86,10 +86,13 @@ typedef enum {
  *               tiles and stores fp32 partial sums to the caller's workspace,
  *               and a second kernel adds them in part order (for grids too
  *               small, or too uneven under the causal mask, to fill the
- *               device).  Automatic: causal grids to about 8 workgroups per
- *               compute unit, dense Pass 2 grids smaller than the compute-unit
- *               count to 2 per unit, the dense first backward to 8 per unit;
- *               never for blocks of fewer than 1024 streamed tiles.
+ *               device).  Automatic, for blocks of at least 1024 streamed
+ *               tiles: causal grids to about 8 workgroups per compute unit,
+ *               dense Pass 2 grids smaller than the compute-unit count to 2
+ *               per unit, the dense first backward to 8 per unit.  For blocks
+ *               of 128 to 1023 streamed tiles: the count with the least
+ *               estimated time (the workspace query tells).  Never for
+ *               shorter blocks.
  *  wave_sets    1 or 2 wave sets per workgroup; two take alternate streamed
  *               tiles and add their fp32 sums through LDS at the end.
  *               Automatic: two when the grid has no more workgroups than the
@@ -255,8 +258,8 @@ int32_t bob_column_layout(int32_t kernel, int32_t dtype, int64_t B, int64_t H, i
  *          code object, held by every device the library runs on until the
  *          process ends.  A split needs parts x 2 x B x Hkv x N x d x 4 bytes
  *          of it.  With parts automatic (opts NULL or opts->parts == 0) the
- *          call uses the largest automatic part count that fits, or runs
- *          unsplit; a forced opts->parts whose split does not fit gives
+ *          call splits blocks of at least 1024 streamed tiles only, into the
+ *          largest automatic part count that fits, or runs unsplit; a forced opts->parts whose split does not fit gives
  *          BOB_ESCRATCH before any launch.
  *  races   every call on one device shares that device's scratch, which
  *          keeps the last call's contents (a split writes every element it

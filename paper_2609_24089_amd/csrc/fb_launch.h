@@ -198,8 +198,13 @@ constexpr int kMaxParts = 8;
 constexpr int64_t kLongChain = 16384;
 constexpr int kSectionTiles = 1024;
 
+// Automatic part counts of column blocks of at least kLongBlock streamed
+// iterations follow resolve_parts(), shorter ones down to min_iters iterations
+// the cost estimate of short_block_parts().
+constexpr int64_t kLongBlock = 1024, kShortBlock = 128;
 struct ColumnOpts {
   int parts = 0, wave_sets = 0, flush_tiles = 0;
+  int64_t min_iters = kShortBlock;
 };
 struct ColumnPlan {
   Grid g{0, 0};
@@ -211,9 +216,19 @@ struct ColumnPlan {
 // Compute units of the current device (0 if it cannot be read).
 int device_cus();
 
-// Automatic (requested = 0) or forced part count for a column grid of
-// `workgroups` with `iters` streamed iterations per block.
-int resolve_parts(int requested, int workgroups, bool causal, bool pass2, int64_t iters);
+// Automatic part count for a column grid of `workgroups` with at least
+// kLongBlock streamed iterations per block.
+int resolve_parts(int workgroups, bool causal, bool pass2);
+
+// A column grid as short_block_parts() prices it.
+struct ColumnCost {
+  int workgroups, blocks;    // grid, column blocks per key/value head
+  int resident, resident1;   // workgroups per CU: split form, unsplit form
+  int64_t iters, plane;      // streamed iterations per block, elements of one output
+  double tile_us;            // MFMA time of one streamed tile of one workgroup
+  bool causal, two_sets;     // two_sets: unsplit, two wave sets would share the stream
+};
+int short_block_parts(const ColumnCost& c);
 
 // Automatic (requested = 0: two sets when the grid has no more workgroups
 // than the device has CUs) or forced (1, 2) wave sets.
@@ -242,6 +257,14 @@ inline int64_t column_workspace_bytes(const Problem& p, int parts) {
   return parts > 1 ? (int64_t)parts * 2 * p.B * p.Hkv * p.N * p.d * (int64_t)sizeof(float) : 0;
 }
 
+// Microseconds of the MFMA work of one streamed tile of one workgroup of a
+// column kernel on a CU, at 85% of the rate a large matrix product
+// reached (1366 TFLOP/s bf16, 154 fp32, on 256 CUs).
+template <typename T, int D, bool kPass2> constexpr double column_tile_us(int rows) {
+  constexpr double per_cu = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / (kXCDs * kCUsPerXCD);  // FLOP per us
+  return 2.0 * (kPass2 ? 8 : 4) * kBS * rows * D / per_cu;
+}
+
 template <typename T, int D, bool kPass2, bool kF>
 struct ColumnShape {
   static constexpr Shape kS =
@@ -249,6 +272,29 @@ struct ColumnShape {
   static constexpr bool kTwoFit =
       kS.mr > 0 && two_sets_fit<T, D, kS.mr, kS.nw, kS.occ, kS.st, kPass2 ? 3 : 2, kPass2 ? 4 : 2, kS.kl != 0>();
 };
+
+// The split form of a column kernel.
+template <typename T, int D, bool kPass2, bool kF> constexpr auto parts_kernel() {
+  constexpr Shape s = ColumnShape<T, D, kPass2, kF>::kS;
+  if constexpr (kPass2)
+    return &bob_pass2_kernel<T, D, s.mr, s.nw, s.occ, s.st, true, 1, s.pf != 0, true, kF>;
+  else
+    return &attn_bwd_cols_kernel<T, D, s.mr, s.nw, s.occ, s.st, true, 1, true, kF, s.kl != 0>;
+}
+
+// Workgroups of a column kernel that fit one CU, in its split or its (one wave
+// set) unsplit form.
+template <typename T, int D, bool kPass2, bool kF> int columns_resident(bool split) {
+  constexpr Shape s = ColumnShape<T, D, kPass2, kF>::kS;
+  if (split) return resident_blocks<parts_kernel<T, D, kPass2, kF>()>(64 * s.nw);
+  if constexpr (kPass2)
+    return resident_blocks<&bob_pass2_kernel<T, D, s.mr, s.nw, s.occ, s.st, true, 1, s.pf != 0, false, kF>>(64 * s.nw);
+  else
+    return resident_blocks<&attn_bwd_cols_kernel<T, D, s.mr, s.nw, s.occ, s.st, true, 1, false, kF, s.kl != 0>>(64 *
+                                                                                                             s.nw);
+}
+extern template int columns_resident<bf16, 128, true, false>(bool);  // built in fb_passes_d128.hip, with their kernels
+extern template int columns_resident<bf16, 128, true, true>(bool);
 
 // Plan of a validated, non-empty, supported problem.  BOB_EINVAL for a
 // request out of range, BOB_EUNSUPPORTED for sections requested where the
@@ -259,15 +305,29 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
     return BOB_EINVAL;
   using S0 = ColumnShape<T, D, kPass2, false>;
   using SF = ColumnShape<T, D, kPass2, true>;
-  auto fill = [&](const Shape& s, bool two_fit) {
+  auto fill = [&](auto shape, auto f) {
+    constexpr Shape s = decltype(shape)::kS;
+    constexpr bool two_fit = decltype(shape)::kTwoFit;
     ColumnPlan c;
     c.g = grid_for(p, 16 * s.mr * s.nw, true);
-    c.parts = resolve_parts(o.parts, c.g.total, p.causal != 0, kPass2, column_iters(p));
+    const int64_t iters = column_iters(p);
+    if (o.parts > 0) {
+      c.parts = o.parts;
+    } else if (iters >= kLongBlock) {
+      c.parts = resolve_parts(c.g.total, p.causal != 0, kPass2);
+    } else if (iters >= o.min_iters) {
+      const bool gpu = device_cus() > 0;
+      const int resident = gpu ? columns_resident<T, D, kPass2, decltype(f)::value>(true) : 1;
+      const int resident1 = gpu ? columns_resident<T, D, kPass2, decltype(f)::value>(false) : 1;
+      c.parts = short_block_parts({c.g.total, c.g.nRB, resident, resident1, iters, p.B * p.Hkv * p.N * p.d,
+                                   column_tile_us<T, D, kPass2>(16 * s.mr * s.nw), p.causal != 0,
+                                   two_fit && resolve_two_sets(o.wave_sets, c.g.total)});
+    }
     if ((int64_t)c.g.total * c.parts > INT32_MAX) c.parts = 1;
     c.sets = (c.parts == 1 && two_fit && resolve_two_sets(o.wave_sets, c.g.total)) ? 2 : 1;
     return c;
   };
-  ColumnPlan c = fill(S0::kS, S0::kTwoFit);
+  ColumnPlan c = fill(S0{}, std::false_type{});
   int ft = o.flush_tiles;
   if (ft == 0) {
     const int64_t per = (int64_t)c.parts * c.sets;
@@ -275,8 +335,8 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
     ft = (SF::kS.mr > 0 && chain > kLongChain) ? kSectionTiles : -1;
   }
   if (ft > 0) {
-    if (SF::kS.mr == 0) return BOB_EUNSUPPORTED;
-    c = fill(SF::kS, SF::kTwoFit);
+    if constexpr (SF::kS.mr == 0) return BOB_EUNSUPPORTED;
+    else c = fill(SF{}, std::true_type{});
     c.flush_tiles = ft;
   }
   // Wide Pass 2 workgroups on dense grids that fill every CU with them
@@ -334,8 +394,7 @@ int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const vo
     (void)hipGetLastError();
     if (cp.parts > 1) {
       // each column block split over cp.parts workgroups, then one reduction
-      hipLaunchKernelGGL((attn_bwd_cols_kernel<T, D, cc.mr, cc.nw, cc.occ, cc.st, true, 1, true, kF, cc.kl != 0>),
-                         dim3(gc.total * cp.parts), dim3(64 * cc.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+      hipLaunchKernelGGL((parts_kernel<T, D, false, kF>()), dim3(gc.total * cp.parts), dim3(64 * cc.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                          (const T*)dO, L, Dv, (T*)dK, (T*)dV, (int)p.N, gc.nRB, gc.total, p.scale, p.causal,
                          0, group(p), parts_ws, cp.parts, cp.flush_tiles);
       const int64_t plane = p.B * p.Hkv * p.N * p.d;
@@ -462,8 +521,7 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
     (void)hipGetLastError();
     if (cp.parts > 1) {
       // each column block split over cp.parts workgroups, then one reduction
-      hipLaunchKernelGGL((bob_pass2_kernel<T, D, c.mr, c.nw, c.occ, c.st, true, 1, c.pf != 0, true, kF>),
-                         dim3(g.total * cp.parts), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+      hipLaunchKernelGGL((parts_kernel<T, D, true, kF>()), dim3(g.total * cp.parts), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                          (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt,
                          (int)p.N, g.nRB, g.total, p.scale, p.causal, 0, group(p), parts_ws, cp.parts,
                          cp.flush_tiles);

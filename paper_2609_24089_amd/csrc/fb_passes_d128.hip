@@ -18,4 +18,7 @@ template int32_t launch_pass2<bf16, 128>(const Problem&, const void*, const void
                                          const float*, const float*, void*, void*, hipStream_t, const ColumnPlan&,
                                          float*);
 
+template int columns_resident<bf16, 128, true, false>(bool);
+template int columns_resident<bf16, 128, true, true>(bool);
+
 }  // namespace fb

@@ -29,7 +29,7 @@ int device_cus() {
     return BOB_EUNSUPPORTED;                                                     \
   } while (0)
 
-// Automatic choice (requested = 0), from interleaved timing at B1 H16 N16384
+// Automatic choice for long blocks, from interleaved timing at B1 H16 N16384
 // d128 bf16 with 1, 2, 4 and 16 key/value heads.  Causal: a column block's
 // work grows with the query tiles at or below its diagonal, and splitting
 // until there are about 8 jobs per CU made the heaviest block's share short
@@ -38,21 +38,64 @@ int device_cus() {
 // only gain was filling both workgroup slots of each CU on a grid smaller
 // than the CU count (6% with one key/value head, against two wave sets in
 // one workgroup).  The dense first backward gained from the same 8 jobs per
-// CU as the causal one (9-18% with 1 and 4 key/value heads).  Either kernel
-// only splits blocks of at least 1024 streamed iterations (query heads per
-// group x 32-row query tiles): on the causal B4 H12 problems at N = 2048 and
-// 4096 (64 and 128 iterations), the parts' fp32 round trip through HBM cost
-// more than the balance gained (up to 14% slower), while every gain above
-// came from blocks of 2048 iterations or more.  Requested 1..8: that many.
-int resolve_parts(int requested, int workgroups, bool causal, bool pass2, int64_t iters) {
-  if (requested >= 1) return requested;
-  if (workgroups <= 0 || iters < 1024) return 1;
+// CU as the causal one (9-18% with 1 and 4 key/value heads).
+int resolve_parts(int workgroups, bool causal, bool pass2) {
   const int cus = device_cus();
   const bool fill_only = pass2 && !causal;
-  if (cus <= 0 || (fill_only && workgroups > cus)) return 1;
+  if (workgroups <= 0 || cus <= 0 || (fill_only && workgroups > cus)) return 1;
   const int64_t target = (int64_t)(fill_only ? 2 : 8) * cus;
   const int64_t parts = (target + workgroups - 1) / workgroups;
   return parts < 2 ? 1 : (int)std::min<int64_t>(parts, kMaxParts);
+}
+
+// Automatic choice for blocks of kShortBlock up to kLongBlock iterations: the
+// part count with the least estimated time.  Equal (dense) blocks cost the
+// rounds of the fullest CU, where a partial round of n workgroups takes half of
+// a full one and n / resident of the other half; causal blocks the larger of the mean load per CU and the
+// heaviest block's share on a CU of its own; a split adds its parts' fp32 round
+// trip through memory (at 4 TB/s) and a launch.  Two wave sets count as two
+// workgroups of half the stream on one CU.  Measured, unsplit -> chosen (us): B1 H16 Hkv4
+// N4099 d128 causal Pass 2 606 -> 281 (4 parts), first backward 721 -> 277 (8);
+// dense 793 -> 610 (3), 877 -> 542 (3); B1 H8 Hkv1 N1024 d128 causal Pass 2
+// 258 -> 51 (8); B1 H1 N8192 d64 causal Pass 2 230 -> 64 (8); B1 H4 N4096 d64
+// Pass 2 121 -> 78 (4).  Below kShortBlock iterations a launch and the round
+// trip cost about what the split gains (B2 H4 N777 d128, 25 iterations: 35 ->
+// 31), and the causal B4 H12 grids at N = 2048 and 4096 (64 and 128) lost up to
+// 14%.
+int short_block_parts(const ColumnCost& c) {
+  const int cus = device_cus();
+  if (cus <= 0 || c.workgroups <= 0) return 1;
+  // a round of n < resident workgroups on a CU, against a full round
+  auto partial = [](int n, int resident) {
+    return n == 0 ? 0.0 : 0.5 + 0.5 * n / resident;
+  };
+  auto cost = [&](int parts) {
+    const int sets = parts == 1 && c.two_sets ? 2 : 1;
+    const int resident = sets == 2 ? 2 : parts == 1 ? c.resident1 : c.resident;
+    const double share = (double)((c.iters + parts * sets - 1) / (parts * sets));
+    double t;
+    if (c.causal) {
+      const double mean = 0.5 * (1.0 + 1.0 / c.blocks) * c.iters * c.workgroups / ((double)cus * resident);
+      t = std::max(mean, share * (sets < resident ? partial(sets, resident) : 1.0));
+    } else {
+      const int64_t k = ((int64_t)c.workgroups * parts + cus - 1) / cus * sets;
+      t = share * ((double)(k / resident) + partial((int)(k % resident), resident));
+    }
+    t *= c.tile_us * resident;
+    if (parts > 1) t += 4.0 + 16.0 * parts * (double)c.plane / 4e6;
+    return t;
+  };
+  int best = 1;
+  const double whole = cost(1);
+  double least = 0.85 * whole;  // a split has to gain more than the estimate's error
+  for (int parts = 2; parts <= kMaxParts; ++parts) {
+    const double t = cost(parts);
+    if (t < least) {
+      best = parts;
+      least = t;
+    }
+  }
+  return best;
 }
 
 static ColumnOpts opts_of(const bob_column_opts* o) {
@@ -156,14 +199,18 @@ static void* scratch_ptr() {
 // The layout of Pass 2 with its workspace in `scratch`: as requested; when
 // the part count is automatic and its workspace would not fit, the largest
 // part count that fits (or none).  A forced part count that does not fit
-// gives BOB_ESCRATCH.
+// gives BOB_ESCRATCH.  Automatic splits here stay those of long blocks: calls
+// that overlap race on the scratch buffer, so a call on short blocks, which
+// callers may run on several streams at once, does not start to use it.
 static int32_t noalloc_plan(const Problem& p, const ColumnOpts& o, ColumnPlan* c) {
-  int32_t rc = column_plan(p, true, o, c);
+  ColumnOpts long_only = o;
+  long_only.min_iters = kLongBlock;
+  int32_t rc = column_plan(p, true, long_only, c);
   if (rc != BOB_OK || column_workspace_bytes(p, c->parts) <= kScratchBytes) return rc;
   if (o.parts != 0) return BOB_ESCRATCH;
   const int64_t per_part = column_workspace_bytes(p, 2) / 2;
   const int fit = (int)std::min<int64_t>(kScratchBytes / per_part, kMaxParts);
-  ColumnOpts capped = o;
+  ColumnOpts capped = long_only;
   capped.parts = fit >= 2 ? std::min(fit, c->parts) : 1;
   return column_plan(p, true, capped, c);
 }
