@@ -15,6 +15,8 @@ LIB = os.path.join(HERE, "libflashbob.so")
 # Translation units and the extra flags each is compiled with.
 SOURCES = [
     ("flashbob.hip", []),
+    ("fb_rows_small.hip", []),
+    ("fb_pass1_small.hip", []),
     ("fb_passes_d128.hip", ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]),
 ]
 

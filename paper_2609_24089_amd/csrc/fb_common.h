@@ -702,6 +702,62 @@ __device__ __forceinline__ void merge_wave_sets(floatx4 (&x)[A][B], floatx4 (&y)
   one(y);
 }
 
+// ---------------------------------------------------------------------------
+// Wave sets of the row kernels, for grids with fewer row blocks than compute
+// units: the workgroup's KS sets of NW waves own the same query rows and take
+// the streamed key tiles round-robin (set ks tiles ks, ks + KS, ...), each
+// through its own LDS ring.  Every set runs the same number of iterations (the
+// loop's barriers are workgroup-wide); an iteration past the end loads the last
+// tile again and skips the math.  At the end the sets add their sums through
+// LDS, and set ks finishes and stores the 16-dim output blocks nb with
+// nb % KS == ks.
+// ---------------------------------------------------------------------------
+template <int KS>
+struct RowSplit {
+  int ks, n;  // this set, tiles of the row block
+  __device__ __forceinline__ int iterations() const { return KS == 1 ? n : (n + KS - 1) / KS; }
+  __device__ __forceinline__ int tile(int it) const { return KS == 1 ? it : min(ks + KS * it, n - 1); }
+  __device__ __forceinline__ bool live(int it) const { return KS == 1 || ks + KS * it < n; }
+  __device__ __forceinline__ bool owns(int nb) const { return KS == 1 || nb % KS == ks; }
+};
+
+// LDS of a row kernel: the tile ring of each set and, with several sets, two
+// row scalars per row and set.
+template <typename T, int D, int NTENS, int NSTAGE, int KS, int ROWS>
+struct RowSmem {
+  T lds[KS][NSTAGE][NTENS * Geo<T, D>::kTileElems];
+  float sc[2][KS][ROWS];
+};
+template <typename T, int D, int NTENS, int NSTAGE, int ROWS>
+struct RowSmem<T, D, NTENS, NSTAGE, 1, ROWS> {
+  T lds[1][NSTAGE][NTENS * Geo<T, D>::kTileElems];
+};
+
+// Sum one accumulator over the sets: every wave stores the blocks it does not
+// own, and the owner of a block adds the other sets' copies to its own, set
+// ks + 1 first (a fixed order).  Every wave calls it (two barriers); buf may
+// alias the tile rings, whose last use precedes the loop's last barrier.
+template <int KS, int NW, int A, int B>
+__device__ __forceinline__ void merge_row_sets(floatx4 (&x)[A][B], int ks, int wl, floatx4 FB_LDS* buf) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+    if (a % KS != ks) {
+#pragma unroll
+      for (int b = 0; b < B; ++b) buf[((ks * NW + wl) * (A * B) + a * B + b) * 64 + lane] = x[a][b];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+    if (a % KS == ks) {
+#pragma unroll
+      for (int q = 1; q < KS; ++q)
+#pragma unroll
+        for (int b = 0; b < B; ++b) x[a][b] += buf[(((ks + q) % KS * NW + wl) * (A * B) + a * B + b) * 64 + lane];
+    }
+  __syncthreads();
+}
+
 // Streamed per-row fp32 scalars (L, D, alpha, E) for one tile, copied HBM ->
 // LDS with global_load_lds_dword: one wave instruction moves two kBS-float
 // vectors (lanes 0..31 read `a`, lanes 32..63 read `b`) to dst[0 .. 63].

@@ -36,14 +36,14 @@ namespace fb {
 // Streamed: K, V.  Online softmax against a reference row maximum that
 // moves only when a row has grown past it by more than 2^8.
 // ===========================================================================
-template <typename T, int D, int MR, int NW, int OCC, int NSTAGE>
-__global__ __launch_bounds__(NW * 64, OCC) void attn_fwd_kernel(
+template <typename T, int D, int MR, int NW, int OCC, int NSTAGE, int KS = 1>
+__global__ __launch_bounds__(KS * NW * 64, OCC) void attn_fwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     T* __restrict__ O, float* __restrict__ L, int N, int nRB, int total, float scale, int causal, int resident, int grp) {
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BR = 16 * MR * NW;
-  __shared__ __attribute__((aligned(16))) T lds[NSTAGE][2 * G::kTileElems];
+  __shared__ __attribute__((aligned(16))) RowSmem<T, D, 2, NSTAGE, KS, BR> sm;
 
   int bh, rb;
   if (resident > 0)
@@ -53,7 +53,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_fwd_kernel(
   const int64_t hoff = (int64_t)bh * N * D;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int row0 = rb * BR + wave_id() * 16 * MR;
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
+  const int wl = KS == 1 ? wave_id() : wave_id() % NW;                           // wave within its set
+  const int row0 = rb * BR + wl * 16 * MR;
 
   u32x4 qf[MR][G::kChunks];
 #pragma unroll
@@ -130,15 +132,16 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_fwd_kernel(
   const T* const src[2] = {K + kvoff, V + kvoff};
   const int nT = (N + kBS - 1) / kBS;
   const int it_end = causal ? min(nT, (min(rb * BR + BR, N) - 1) / kBS + 1) : nT;
-  const TileCopy<T, D, NW, 2> copy(wave_id());
+  const RowSplit<KS> sp{ks, it_end};
+  const TileCopy<T, D, NW, 2> copy(wl);
   stream_loop<NSTAGE, tile_loads<T, D, NW, 2>()>(
-      0, it_end,
-      [&](int it, int st) { copy.issue(src, (T FB_LDS*)lds[st], it * kBS, N); },
+      0, sp.iterations(),
+      [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
-        const int s0 = it * kBS;
-        const int mode = tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0);
+        const int s0 = sp.tile(it) * kBS;
+        const int mode = sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0;
         if (mode == 0) return;
-        const T FB_LDS* Ks = (const T FB_LDS*)lds[st];
+        const T FB_LDS* Ks = (const T FB_LDS*)sm.lds[ks][st];
         const T FB_LDS* Vs = Ks + G::kTileElems;
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
@@ -160,15 +163,45 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_fwd_kernel(
           for (int mb = 0; mb < MR; ++mb) acc[nb][mb] = E::mma_acc(a, pf[mb], acc[nb][mb]);
         }
       });
+  float lt[MR];
+#pragma unroll
+  for (int mb = 0; mb < MR; ++mb) lt[mb] = group_sum(lsum[mb]);
+  if constexpr (KS > 1) {
+    // bring the sets to one reference (a set without a valid tile has the
+    // reference -1e30 and zero sums), then add them
+#pragma unroll
+    for (int mb = 0; mb < MR; ++mb)
+      if (g == 0) {
+        sm.sc[0][ks][16 * (wl * MR + mb) + j] = mrun[mb];
+        sm.sc[1][ks][16 * (wl * MR + mb) + j] = lt[mb];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < MR; ++mb) {
+      const int at = 16 * (wl * MR + mb) + j;
+      float m = sm.sc[0][0][at], sum = 0.f;
+#pragma unroll
+      for (int q = 1; q < KS; ++q) m = fmaxf(m, sm.sc[0][q][at]);
+#pragma unroll
+      for (int q = 0; q < KS; ++q) sum = __builtin_fmaf(sm.sc[1][q][at], fast_exp2(sm.sc[0][q][at] - m), sum);
+      const float corr = fast_exp2(mrun[mb] - m);
+      mrun[mb] = m;
+      lt[mb] = sum;
+#pragma unroll
+      for (int nb = 0; nb < G::kNB; ++nb) acc[nb][mb] *= corr;
+    }
+    static_assert(sizeof(sm.lds) >= (size_t)KS * NW * G::kNB * MR * 1024, "set merge buffer");
+    merge_row_sets<KS, NW>(acc, ks, wl, (floatx4 FB_LDS*)&sm.lds[0][0][0]);
+  }
 #pragma unroll
   for (int mb = 0; mb < MR; ++mb) {
     const int row = row0 + 16 * mb + j;
-    const float lt = group_sum(lsum[mb]);
-    const float inv = 1.f / lt;
+    const float inv = 1.f / lt[mb];
     if (row < N) {
 #pragma unroll
-      for (int nb = 0; nb < G::kNB; ++nb) E::store4(O + hoff + (int64_t)row * D + 16 * nb + 4 * g, acc[nb][mb] * inv);
-      if (g == 0) L[(int64_t)bh * N + row] = (mrun[mb] + __log2f(lt)) * kLn2;
+      for (int nb = 0; nb < G::kNB; ++nb)
+        if (sp.owns(nb)) E::store4(O + hoff + (int64_t)row * D + 16 * nb + 4 * g, acc[nb][mb] * inv);
+      if (g == 0 && ks == 0) L[(int64_t)bh * N + row] = (mrun[mb] + __log2f(lt[mb])) * kLn2;
     }
   }
 }
@@ -178,15 +211,15 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_fwd_kernel(
 // dS = P (dP - D), dP = dO V^T (eqs. 2-3).  Stationary: Q, dO rows.
 // Streamed: K, V.  Writes D and dQ once per row; no atomics.
 // ===========================================================================
-template <typename T, int D, int MR, int NW, int OCC, int NSTAGE>
-__global__ __launch_bounds__(NW * 64, OCC) void attn_bwd_rows_kernel(
+template <typename T, int D, int MR, int NW, int OCC, int NSTAGE, int KS = 1>
+__global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_rows_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ O, const T* __restrict__ dO, const float* __restrict__ L,
     T* __restrict__ dQ, float* __restrict__ Dout, int N, int nRB, int total, float scale, int causal, int resident, int grp) {
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BR = 16 * MR * NW;
-  __shared__ __attribute__((aligned(16))) T lds[NSTAGE][2 * G::kTileElems];
+  __shared__ __attribute__((aligned(16))) RowSmem<T, D, 2, NSTAGE, KS, BR> sm;
 
   int bh, rb;
   if (resident > 0)
@@ -196,7 +229,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_bwd_rows_kernel(
   const int64_t hoff = (int64_t)bh * N * D;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int row0 = rb * BR + wave_id() * 16 * MR;
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
+  const int wl = KS == 1 ? wave_id() : wave_id() % NW;                           // wave within its set
+  const int row0 = rb * BR + wl * 16 * MR;
 
   u32x4 qf[MR][G::kChunks], dof[MR][G::kChunks];
   float lb[MR], drow[MR];
@@ -212,7 +247,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_bwd_rows_kernel(
     for (int kk = 0; kk < G::kChunks; ++kk) part += E::dot_chunk(dof[mb][kk], of[kk]);
     drow[mb] = group_sum(part);
     lb[mb] = row < N ? L[(int64_t)bh * N + row] * kLog2e : 0.f;
-    if (g == 0 && row < N) Dout[(int64_t)bh * N + row] = drow[mb];
+    if (g == 0 && ks == 0 && row < N) Dout[(int64_t)bh * N + row] = drow[mb];
   }
 
   floatx4 acc[G::kNB][MR];
@@ -241,15 +276,16 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_bwd_rows_kernel(
   const T* const src[2] = {K + kvoff, V + kvoff};
   const int nT = (N + kBS - 1) / kBS;
   const int it_end = causal ? min(nT, (min(rb * BR + BR, N) - 1) / kBS + 1) : nT;
-  const TileCopy<T, D, NW, 2> copy(wave_id());
+  const RowSplit<KS> sp{ks, it_end};
+  const TileCopy<T, D, NW, 2> copy(wl);
   stream_loop<NSTAGE, tile_loads<T, D, NW, 2>()>(
-      0, it_end,
-      [&](int it, int st) { copy.issue(src, (T FB_LDS*)lds[st], it * kBS, N); },
+      0, sp.iterations(),
+      [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
-        const int s0 = it * kBS;
-        const int mode = tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0);
+        const int s0 = sp.tile(it) * kBS;
+        const int mode = sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0;
         if (mode == 0) return;
-        const T FB_LDS* Ks = (const T FB_LDS*)lds[st];
+        const T FB_LDS* Ks = (const T FB_LDS*)sm.lds[ks][st];
         const T FB_LDS* Vs = Ks + G::kTileElems;
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
@@ -286,12 +322,17 @@ __global__ __launch_bounds__(NW * 64, OCC) void attn_bwd_rows_kernel(
           for (int mb = 0; mb < MR; ++mb) acc[nb][mb] = E::mma_acc(a, dsf[mb], acc[nb][mb]);
         }
       });
+  if constexpr (KS > 1) {
+    static_assert(sizeof(sm.lds) >= (size_t)KS * NW * G::kNB * MR * 1024, "set merge buffer");
+    merge_row_sets<KS, NW>(acc, ks, wl, (floatx4 FB_LDS*)&sm.lds[0][0][0]);
+  }
 #pragma unroll
   for (int mb = 0; mb < MR; ++mb) {
     const int row = row0 + 16 * mb + j;
     if (row < N) {
 #pragma unroll
-      for (int nb = 0; nb < G::kNB; ++nb) E::store4(dQ + hoff + (int64_t)row * D + 16 * nb + 4 * g, acc[nb][mb] * scale);
+      for (int nb = 0; nb < G::kNB; ++nb)
+        if (sp.owns(nb)) E::store4(dQ + hoff + (int64_t)row * D + 16 * nb + 4 * g, acc[nb][mb] * scale);
     }
   }
 }
@@ -552,8 +593,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
 // ===========================================================================
 enum Pass1Form : int { kSixAcc = 0, kWithDQ = 1, kAlphaGiven = 2 };
 
-template <typename T, int D, int MR, int NW, int OCC, int NSTAGE, int kForm, int DSPLIT, int kPF>
-__global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
+template <typename T, int D, int MR, int NW, int OCC, int NSTAGE, int kForm, int DSPLIT, int kPF, int KS = 1>
+__global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass1_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
     const T* __restrict__ O, const T* __restrict__ dO, const T* __restrict__ UQ,
     const T* __restrict__ UK, const T* __restrict__ UV, const float* __restrict__ L,
@@ -565,7 +606,8 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
   constexpr bool kDQ = kForm == kWithDQ;
   constexpr bool kThree = kForm == kAlphaGiven;
   constexpr int BR = 16 * MR * NW;
-  __shared__ __attribute__((aligned(16))) T lds[NSTAGE][4 * G::kTileElems];
+  static_assert(KS == 1 || (kDQ && DSPLIT == 1), "wave sets: the dQ form in one workgroup per row block");
+  __shared__ __attribute__((aligned(16))) RowSmem<T, D, 4, NSTAGE, KS, BR> sm;
 
   int bh, rb;
   if (resident > 0)
@@ -576,7 +618,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
   const int64_t soff = (int64_t)bh * N;
   const int64_t kvoff = (int64_t)(bh / grp) * N * D;  // key/value head of this query head
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int row0 = rb * BR + wave_id() * 16 * MR;
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
+  const int wl = KS == 1 ? wave_id() : wave_id() % NW;                           // wave within its set
+  const int row0 = rb * BR + wl * 16 * MR;
 
   u32x4 qf[MR][G::kChunks], uqf[MR][G::kChunks], dof[MR][G::kChunks];
   float lb[MR], drow[MR], arow[MR];
@@ -743,15 +787,16 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
   const T* const src[4] = {K + kvoff, V + kvoff, UK + kvoff, UV + kvoff};
   const int nT = (N + kBS - 1) / kBS;
   const int it_end = causal ? min(nT, (min(rb * BR + BR, N) - 1) / kBS + 1) : nT;
-  const TileCopy<T, D, NW, 4> copy(wave_id());
+  const RowSplit<KS> sp{ks, it_end};
+  const TileCopy<T, D, NW, 4> copy(wl);
   stream_loop<NSTAGE, tile_loads<T, D, NW, 4>()>(
-      0, it_end,
-      [&](int it, int st) { copy.issue(src, (T FB_LDS*)lds[st], it * kBS, N); },
+      0, sp.iterations(),
+      [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
-        const int s0 = it * kBS;
-        const int mode = tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0);
+        const int s0 = sp.tile(it) * kBS;
+        const int mode = sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0;
         if (mode == 0) return;
-        const T FB_LDS* Ks = (const T FB_LDS*)lds[st];
+        const T FB_LDS* Ks = (const T FB_LDS*)sm.lds[ks][st];
         // bf16 d = 128: LLVM's exp-interleave scheduling strategy for the tile
         // (Pass 1 1.1-1.5% faster; slower at d = 64)
         if constexpr (std::is_same_v<T, bf16> && D == 128) __builtin_amdgcn_iglp_opt(3);
@@ -769,6 +814,21 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
         accumulate(Ks, f0);
       });
 
+  if constexpr (KS > 1) {
+#pragma unroll
+    for (int mb = 0; mb < MR; ++mb) {
+      const float al = group_sum(alpha[mb]), es = group_sum(e0[mb]);
+      if (g == 0) {
+        sm.sc[0][ks][16 * (wl * MR + mb) + j] = al;
+        sm.sc[1][ks][16 * (wl * MR + mb) + j] = es;
+      }
+    }
+    static_assert(sizeof(sm.lds) >= (size_t)KS * NW * kNBh * MR * 1024, "set merge buffer");
+    floatx4 FB_LDS* buf = (floatx4 FB_LDS*)&sm.lds[0][0][0];
+    merge_row_sets<KS, NW>(aDO, ks, wl, buf);  // its barriers publish the scalars too
+    merge_row_sets<KS, NW>(aOM, ks, wl, buf);
+    merge_row_sets<KS, NW>(aB, ks, wl, buf);
+  }
   // epilogue (eq. 8; for kAlphaGiven the delayed E correction alone)
 #pragma unroll
   for (int mb = 0; mb < MR; ++mb) {
@@ -786,16 +846,29 @@ __global__ __launch_bounds__(NW * 64, OCC) void bob_pass1_kernel(
       }
       continue;
     }
-    const float al = group_sum(alpha[mb]);
-    const float e0s = group_sum(e0[mb]);
+    float al, e0s;
+    if constexpr (KS > 1) {
+      const int at = 16 * (wl * MR + mb) + j;
+      al = sm.sc[0][0][at];
+      e0s = sm.sc[1][0][at];
+#pragma unroll
+      for (int q = 1; q < KS; ++q) {
+        al += sm.sc[0][q][at];
+        e0s += sm.sc[1][q][at];
+      }
+    } else {
+      al = group_sum(alpha[mb]);
+      e0s = group_sum(e0[mb]);
+    }
     const float ee = e0s - al * drow[mb];
     if (row < N) {
-      if (g == 0 && write_scalars) {
+      if (g == 0 && write_scalars && ks == 0) {
         alpha_out[soff + row] = al;
         E_out[soff + row] = ee;
       }
 #pragma unroll
       for (int nb = 0; nb < kNBh; ++nb) {
+        if (!sp.owns(nb)) continue;
         const int64_t off = hoff + (int64_t)row * D + 16 * (nb0 + nb) + 4 * g;
         const floatx4 o = E::load4(O + off);
         E::store4(dOt + off, aDO[nb][mb] - al * o);

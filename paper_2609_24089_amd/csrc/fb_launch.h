@@ -257,12 +257,14 @@ inline int64_t column_workspace_bytes(const Problem& p, int parts) {
   return parts > 1 ? (int64_t)parts * 2 * p.B * p.Hkv * p.N * p.d * (int64_t)sizeof(float) : 0;
 }
 
+// FLOP per us of one CU at 85% of the rate a large matrix product reached (1366
+// TFLOP/s bf16, 154 fp32, on 256 CUs).
+template <typename T> constexpr double kCuRate = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / (kXCDs * kCUsPerXCD);
+
 // Microseconds of the MFMA work of one streamed tile of one workgroup of a
-// column kernel on a CU, at 85% of the rate a large matrix product
-// reached (1366 TFLOP/s bf16, 154 fp32, on 256 CUs).
+// column kernel on a CU.
 template <typename T, int D, bool kPass2> constexpr double column_tile_us(int rows) {
-  constexpr double per_cu = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / (kXCDs * kCUsPerXCD);  // FLOP per us
-  return 2.0 * (kPass2 ? 8 : 4) * kBS * rows * D / per_cu;
+  return 2.0 * (kPass2 ? 8 : 4) * kBS * rows * D / kCuRate<T>;
 }
 
 template <typename T, int D, bool kPass2, bool kF>
@@ -369,12 +371,115 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
   return BOB_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Row kernels on small grids: blocks of 16 nw query rows (nw = 4, 2, 1), with
+// as many wave sets (RowSplit) as the LDS holds.
+// ---------------------------------------------------------------------------
+struct RowShape {
+  int nw, ks, occ;
+};
+// The wave sets of a row kernel that streams `tensors` tensors: a power of two
+// whose two-stage rings fit 160 KB next to the row scalars, in at most
+// `max_waves` waves.
+template <typename T, int D> constexpr RowShape row_shape(int nw, int tensors, int max_waves, int occ) {
+  const int ring = 2 * tensors * Geo<T, D>::kTileElems * (int)sizeof(T);
+  int ks = 1;
+  while (2 * ks * nw <= max_waves && 2 * ks * (ring + 2 * 16 * nw * 4) <= 160 * 1024) ks *= 2;
+  return {nw, ks, std::max(occ, ks * nw / 4)};
+}
+// One form of a row kernel as row_form() prices it: 16-row blocks per
+// workgroup, wave sets, workgroups that fit one CU (0: not built).
+struct RowForm {
+  int blocks, sets, resident;
+};
+// Index of the form with the least estimated time.  `contractions`: tile
+// contractions of the kernel per streamed tile; rate: FLOP per us of one CU.
+int row_form(const Problem& p, int contractions, double rate, std::initializer_list<RowForm> forms);
+
+template <typename T, int D, int NW> struct FwdSmall {
+  static constexpr RowShape kS = row_shape<T, D>(NW, 2, 16, Cfg<T, D>::kFwd.occ);
+  static constexpr auto kKernel = &attn_fwd_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
+  static RowForm form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
+                        hipStream_t s) {
+    const Grid g = grid_for(p, 16 * NW);
+    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
+    return finish_launch();
+  }
+};
+
+template <typename T, int D, int NW> struct RowsSmall {
+  // two operands and an accumulator of 16 rows fit four waves per SIMD up to 128-byte rows
+  static constexpr RowShape kS = row_shape<T, D>(NW, 2, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kRows.occ);
+  static constexpr auto kKernel = &attn_bwd_rows_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
+  static RowForm form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
+                        const float* L, void* dQ, float* Dv, hipStream_t s) {
+    const Grid g = grid_for(p, 16 * NW);
+    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
+                       group(p));
+    return finish_launch();
+  }
+};
+
+template <typename T, int D, int NW> struct Pass1Small {
+  static constexpr RowShape kS = row_shape<T, D>(NW, 4, 8, Cfg<T, D>::kP1.occ);
+  // where no second set fits, four blocks are the whole-block shape itself and
+  // not built here again (their place is held by the two-block kernel, never run)
+  static constexpr bool kBuilt = NW != 4 || kS.ks > 1;
+  static constexpr auto kKernel =
+      &bob_pass1_kernel<T, D, 1, kBuilt ? NW : 2, kS.occ, 2, kWithDQ, 1, Cfg<T, D>::kP1.pf, kS.ks>;
+  static RowForm form() { return {NW, kS.ks, kBuilt ? resident_blocks<kKernel>(64 * NW * kS.ks) : 0}; }
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
+                        const void* UQ, const void* UK, const void* UV, const float* L, const float* Dv,
+                        const void* dQ, void* Qt, void* dOt, float* alpha, float* E, hipStream_t s) {
+    if (!kBuilt) return BOB_EUNSUPPORTED;
+    const Grid g = grid_for(p, 16 * NW);
+    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (const T*)O, (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, (const T*)dQ,
+                       (const float*)nullptr, (T*)Qt, (T*)dOt, alpha, E, (int)p.N, g.nRB, g.total, p.scale, p.causal,
+                       res, group(p));
+    return finish_launch();
+  }
+};
+
+// Built in fb_rows_small.hip, fb_pass1_small.hip and (Pass 1 at bf16 d = 128)
+// fb_passes_d128.hip.
+#define FB_ROWS_SMALL(EXT, T, D) \
+  EXT template struct FwdSmall<T, D, 4>; EXT template struct FwdSmall<T, D, 2>; EXT template struct FwdSmall<T, D, 1>; \
+  EXT template struct RowsSmall<T, D, 4>; EXT template struct RowsSmall<T, D, 2>; EXT template struct RowsSmall<T, D, 1>;
+#define FB_PASS1_SMALL(EXT, T, D) \
+  EXT template struct Pass1Small<T, D, 4>; EXT template struct Pass1Small<T, D, 2>; EXT template struct Pass1Small<T, D, 1>;
+#define FB_EACH_BUT_BF16_128(M, EXT) \
+  M(EXT, bf16, 32) M(EXT, bf16, 64) M(EXT, bf16, 256) M(EXT, float, 32) M(EXT, float, 64) M(EXT, float, 128)
+FB_EACH_BUT_BF16_128(FB_ROWS_SMALL, extern)
+FB_ROWS_SMALL(extern, bf16, 128)
+FB_EACH_BUT_BF16_128(FB_PASS1_SMALL, extern)
+FB_PASS1_SMALL(extern, bf16, 128)
+
 template <typename T, int D>
 int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
                    hipStream_t s) {
   constexpr Shape c = Cfg<T, D>::kFwd;
-  const Grid g = grid_for(p, 16 * c.mr * c.nw);
   constexpr auto kernel = &attn_fwd_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
+  using F4 = FwdSmall<T, D, 4>;
+  using F2 = FwdSmall<T, D, 2>;
+  using F1 = FwdSmall<T, D, 1>;
+  switch (row_form(p, 2, kCuRate<T>,
+                   {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form()})) {
+    case 1: return F4::launch(p, Q, K, V, O, L, s);
+    case 2: return F2::launch(p, Q, K, V, O, L, s);
+    case 3: return F1::launch(p, Q, K, V, O, L, s);
+  }
+  const Grid g = grid_for(p, 16 * c.mr * c.nw);
   const int res = causal_resident<kernel>(p, g, 64 * c.nw);
   (void)hipGetLastError();
   hipLaunchKernelGGL(kernel, dim3(g.total), dim3(64 * c.nw), 0, s,
@@ -426,6 +531,29 @@ int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const vo
   }
 }
 
+template <typename T, int D>
+int32_t launch_bwd_rows(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
+                        const float* L, void* dQ, float* Dv, hipStream_t s) {
+  constexpr Shape cr = Cfg<T, D>::kRows;
+  constexpr auto rows = &attn_bwd_rows_kernel<T, D, cr.mr, cr.nw, cr.occ, cr.st>;
+  using F4 = RowsSmall<T, D, 4>;
+  using F2 = RowsSmall<T, D, 2>;
+  using F1 = RowsSmall<T, D, 1>;
+  switch (row_form(p, 3, kCuRate<T>,
+                   {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw)}, F4::form(), F2::form(), F1::form()})) {
+    case 1: return F4::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+    case 2: return F2::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+    case 3: return F1::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+  }
+  const Grid gr = grid_for(p, 16 * cr.mr * cr.nw);
+  const int res = causal_resident<rows>(p, gr, 64 * cr.nw);
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(rows, dim3(gr.total), dim3(64 * cr.nw), 0, s,
+                     (const T*)Q, (const T*)K, (const T*)V, (const T*)O, (const T*)dO, L, (T*)dQ, Dv,
+                     (int)p.N, gr.nRB, gr.total, p.scale, p.causal, res, group(p));
+  return finish_launch();
+}
+
 // The first backward: the row kernel (dQ, D), then the column kernel (dK, dV)
 // laid out by `cp` (plan_columns<T, D, false>); parts_ws is the caller's
 // workspace when cp.parts > 1.
@@ -433,15 +561,7 @@ template <typename T, int D>
 int32_t launch_bwd(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
                    const void* dO, const float* L, void* dQ, void* dK, void* dV, float* Dv,
                    hipStream_t s, const ColumnPlan& cp, float* parts_ws) {
-  constexpr Shape cr = Cfg<T, D>::kRows;
-  const Grid gr = grid_for(p, 16 * cr.mr * cr.nw);
-  constexpr auto rows = &attn_bwd_rows_kernel<T, D, cr.mr, cr.nw, cr.occ, cr.st>;
-  const int res = causal_resident<rows>(p, gr, 64 * cr.nw);
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(rows, dim3(gr.total), dim3(64 * cr.nw), 0, s,
-                     (const T*)Q, (const T*)K, (const T*)V, (const T*)O, (const T*)dO, L, (T*)dQ, Dv,
-                     (int)p.N, gr.nRB, gr.total, p.scale, p.causal, res, group(p));
-  int32_t rc = finish_launch();
+  const int32_t rc = launch_bwd_rows<T, D>(p, Q, K, V, O, dO, L, dQ, Dv, s);
   if (rc != BOB_OK) return rc;
   if (cp.flush_tiles > 0)
     return launch_bwd_cols<T, D, true>(p, Q, K, V, dO, L, Dv, dK, dV, s, cp, parts_ws);
@@ -456,8 +576,17 @@ int32_t launch_pass1(const Problem& p, const void* Q, const void* K, const void*
                      hipStream_t s) {
   if (dQ != nullptr) {
     constexpr Shape c = Cfg<T, D>::kP1;
-    const Grid g = grid_for(p, 16 * c.mr * c.nw);
     constexpr auto kernel = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kWithDQ, c.ds, c.pf>;
+    using F4 = Pass1Small<T, D, 4>;
+    using F2 = Pass1Small<T, D, 2>;
+    using F1 = Pass1Small<T, D, 1>;
+    switch (row_form(p, 10, kCuRate<T>,
+                     {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form()})) {
+      case 1: return F4::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
+      case 2: return F2::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
+      case 3: return F1::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
+    }
+    const Grid g = grid_for(p, 16 * c.mr * c.nw);
     const int res = causal_resident<kernel>(p, g, 64 * c.nw);
     (void)hipGetLastError();
     hipLaunchKernelGGL(kernel, dim3(g.total, c.ds), dim3(64 * c.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (const T*)O,

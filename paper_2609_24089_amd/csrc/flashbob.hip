@@ -98,6 +98,55 @@ int short_block_parts(const ColumnCost& c) {
   return best;
 }
 
+// Estimated time of a row kernel's forms.  A step (one streamed tile of every
+// wave set on a CU) with n waves' worth of 16-row blocks takes 4.5 + 0.45 n times
+// the MFMA time of one block, n at least the four that occupy every SIMD.  Equal
+// (dense) blocks cost the rounds of the fullest CU, causal ones the larger of
+// the mean load and the heaviest block's steps; kRound is a round's prologue,
+// epilogue and merge of the sets.  The three constants were fitted to 37 shapes
+// (N = 256 to 32768, 1 to 48 heads, both types, every head dim) timed in every
+// form: the choice is on average 1.2% slower than the best form, and at most 23%.
+// Measured, whole blocks -> chosen form (us): bf16 B1 H1 N8192 d64 causal forward
+// 136 -> 34, Pass 1 206 -> 100; B1 H4 N4096 d128 dense 105 -> 48, 229 -> 152; B2
+// H4 N777 d128 26 -> 13, 55 -> 33; fp32 B1 H1 N256 d64 14 -> 7, 46 -> 27.
+int row_form(const Problem& p, int contractions, double rate, std::initializer_list<RowForm> forms) {
+  constexpr int kCUs = kXCDs * kCUsPerXCD;
+  constexpr double kRound = 4.0;
+  const double block_us = 2.0 * contractions * 16 * kBS * (double)p.d / rate;  // one 16-row block, one tile
+  const double tiles = (double)((p.N + kBS - 1) / kBS);
+  int best = 0, i = -1;
+  bool fills = false;
+  double least = 0;
+  for (const RowForm& f : forms) {
+    ++i;
+    if (f.resident == 0) continue;  // not built
+    // whole blocks that fill every slot of the device stay (bf16 B1 H20 N1800
+    // d256 causal, 580 blocks in 512 slots: forward 64 us, 72 in two sets)
+    if (i > 0 && fills) break;
+    const int64_t nRB = (p.N + 16 * f.blocks - 1) / (16 * f.blocks), total = p.B * p.H * nRB;
+    if (i == 0) fills = f.resident > 1 && total > kCUs * f.resident;
+    const double share = std::ceil(tiles / f.sets);
+    auto step = [&](int64_t workgroups) {
+      return block_us * (4.5 + 0.45 * std::max<int64_t>(4, workgroups * f.blocks * f.sets));
+    };
+    const int64_t k = (total + kCUs - 1) / kCUs;  // workgroups of the fullest CU
+    double t;
+    if (p.causal != 0) {
+      const int64_t n = std::min<int64_t>(k, f.resident);
+      const double mean = 0.5 * (share + 1) * total / (double)kCUs / n * step(n);
+      t = std::max(mean, share * step(1));
+    } else {
+      t = share * ((double)(k / f.resident) * step(f.resident) + (k % f.resident != 0 ? step(k % f.resident) : 0));
+    }
+    t += kRound * (double)((k + f.resident - 1) / f.resident);
+    if (i == 0 || t < least) {
+      best = i;
+      least = t;
+    }
+  }
+  return best;
+}
+
 static ColumnOpts opts_of(const bob_column_opts* o) {
   ColumnOpts c;
   if (o != nullptr) {
