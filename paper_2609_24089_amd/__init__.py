@@ -4,8 +4,10 @@ Thin Python binding over libflashbob.so (include/flashbob.h).  The entry
 points keep the C names (the grouped-query variants are chosen from the
 tensor shapes); each one only checks and marshals torch-ROCm tensors
 (device memory and the current stream) and calls the library, so every step
-of the computation runs in the gfx950 kernels.  There is no fallback: if the
-library is missing, importing the binding raises.
+of the computation runs in the gfx950 kernels.  Calls with fresh outputs, the
+current stream and automatic layouts are marshalled natively (_fb_torch,
+csrc/torch_binding.cpp), the others through ctypes.  There is no fallback: if
+the library or the native binding is missing, loading it raises.
 """
 import ctypes
 import os
@@ -21,6 +23,7 @@ BOB_OK, BOB_EINVAL, BOB_EUNSUPPORTED, BOB_ELAUNCH, BOB_ESCRATCH = 0, 1, 2, 3, 4
 BOB_COLUMNS_BWD, BOB_COLUMNS_PASS2 = 0, 1
 
 _lib = None
+_native = None  # csrc/torch_binding.cpp, bound to the loaded library
 
 
 class ColumnOpts(ctypes.Structure):
@@ -37,7 +40,7 @@ class ColumnOpts(ctypes.Structure):
 
 def load_library():
     """Load libflashbob.so (built by paper_2609_24089_amd.build); raise if absent."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -84,8 +87,19 @@ def load_library():
     lib.attn_bob_pass2_cols_gqa_noalloc.restype = i32
     lib.bob_scratch_bytes.argtypes = []
     lib.bob_scratch_bytes.restype = i64
-    _lib = lib
+    from . import _fb_torch
+    _fb_torch.bind(LIB_PATH)
+    _lib, _native = lib, _fb_torch
     return lib
+
+
+def _fast():
+    """The native fast path.  Its functions return None for a call they do not
+    take (anything but plain, valid tensors); the code after them then runs the
+    call through ctypes, or raises what its checks say."""
+    if _native is None:
+        load_library()
+    return _native
 
 
 def status_string(rc):
@@ -210,6 +224,10 @@ def _rows_empty(shape, like):
 def attn_fwd_lse(Q, K, V, scale, causal=False, out=None, stream=None):
     """Forward attention (eq. 1): returns (O, L).  K, V may have fewer heads
     than Q (grouped-query attention, see include/flashbob.h)."""
+    if out is None and stream is None:
+        got = _fast().fwd(Q, K, V, float(scale), bool(causal))
+        if got is not None:
+            return got
     B, H, Hkv, N, d = _check_groups((Q,), (K, V))
     if out is None:
         out = (torch.empty_like(Q), _rows_empty(Q.shape, Q))
@@ -228,6 +246,10 @@ def attn_fwd_lse(Q, K, V, scale, causal=False, out=None, stream=None):
 def attn_bwd(Q, K, V, O, dO, L, scale, causal=False, out=None, stream=None, columns=None):
     """First backward (eqs. 2-3): returns (dQ, dK, dV, D); dK, dV have K's shape.
     columns: ColumnOpts for the dK, dV kernel (None: automatic)."""
+    if out is None and stream is None and columns is None:
+        got = _fast().bwd(Q, K, V, O, dO, L, float(scale), bool(causal))
+        if got is not None:
+            return got
     B, H, Hkv, N, d = _check_groups((Q, O, dO), (K, V))
     _check_rows(Q.shape, L)
     if out is None:
@@ -252,6 +274,10 @@ def attn_bob_pass1_rows(Q, K, V, O, dO, gdQ, gdK, gdV, L, D, scale, causal=False
 
     dQ (the first-backward output) is optional; when given, the kernel uses
     it in place of the R accumulator (see include/flashbob.h)."""
+    if out is None and stream is None:
+        got = _fast().pass1(Q, K, V, O, dO, gdQ, gdK, gdV, L, D, float(scale), bool(causal), dQ)
+        if got is not None:
+            return got
     B, H, Hkv, N, d = _check_groups((Q, O, dO, gdQ), (K, V, gdK, gdV))
     if dQ is not None:
         _check_mats(Q, dQ)
@@ -276,6 +302,10 @@ def attn_bob_pass2_cols(Q, K, V, dO, gdQ, gdK, gdV, L, D, alpha, E, scale, causa
                         columns=None):
     """BoB Pass 2 (column-major): returns (Kt, Vt), with K's shape.
     columns: ColumnOpts for its layout (None: automatic)."""
+    if out is None and stream is None and columns is None:
+        got = _fast().pass2(Q, K, V, dO, gdQ, gdK, gdV, L, D, alpha, E, float(scale), bool(causal))
+        if got is not None:
+            return got
     B, H, Hkv, N, d = _check_groups((Q, dO, gdQ), (K, V, gdK, gdV))
     _check_rows(Q.shape, L, D, alpha, E)
     if out is None:
@@ -364,6 +394,11 @@ def bob(Q, K, V, dO, gdQ, gdK, gdV, scale, causal=False, use_dq=True, stream=Non
     Returns a dict with Qt, Kt, Vt, dOt, alpha, E and the producer state
     O, L, D, dQ, dK, dV.
     """
+    if stream is None and columns is None:
+        got = _fast().bob(Q, K, V, dO, gdQ, gdK, gdV, float(scale), bool(causal), bool(use_dq))
+        if got is not None:
+            O, L, dQ, dK, dV, D, Qt, dOt, alpha, E, Kt, Vt = got
+            return dict(Qt=Qt, Kt=Kt, Vt=Vt, dOt=dOt, alpha=alpha, E=E, O=O, L=L, D=D, dQ=dQ, dK=dK, dV=dV)
     O, L = attn_fwd_lse(Q, K, V, scale, causal, stream=stream)
     dQ, dK, dV, D = attn_bwd(Q, K, V, O, dO, L, scale, causal, stream=stream, columns=columns)
     Qt, dOt, alpha, E = attn_bob_pass1_rows(Q, K, V, O, dO, gdQ, gdK, gdV, L, D, scale, causal,

@@ -26,7 +26,7 @@ head h // (H / Hkv)); their gradients then sum over each group.
 """
 import torch
 
-from . import attn_bob_pass1_rows, attn_bob_pass2_cols, attn_bwd, attn_fwd_lse
+from . import _fast, attn_bob_pass1_rows, attn_bob_pass2_cols, attn_bwd, attn_fwd_lse
 
 
 class _AttentionFn(torch.autograd.Function):
@@ -66,4 +66,9 @@ def attention(q, k, v, scale=None, causal=False):
     second derivatives on the HIP path.  scale defaults to 1/sqrt(d)."""
     if scale is None:
         scale = q.shape[-1] ** -0.5
+    if not torch.compiler.is_compiling():
+        # the same two functions in C++ (csrc/torch_binding.cpp); None for calls it does not take
+        O = _fast().attention(q, k, v, float(scale), bool(causal))
+        if O is not None:
+            return O
     return _AttentionFn.apply(q, k, v, float(scale), bool(causal))
