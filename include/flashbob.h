@@ -89,15 +89,17 @@ typedef enum {
  *               device).  Automatic, for blocks of at least 1024 streamed
  *               tiles: causal grids to about 8 workgroups per compute unit,
  *               dense Pass 2 grids smaller than the compute-unit count to 2
- *               per unit, the dense first backward to 8 per unit.  For blocks
- *               of 128 to 1023 streamed tiles: the count with the least
- *               estimated time (the workspace query tells).  Never for
- *               shorter blocks.
- *  wave_sets    1 or 2 wave sets per workgroup; two take alternate streamed
- *               tiles and add their fp32 sums through LDS at the end.
- *               Automatic: two when the grid has no more workgroups than the
- *               device has compute units (and the shape has room: bf16
- *               d <= 128, fp32 Pass 2 with d <= 64); a split block uses one.
+ *               per unit, the dense first backward to 8 per unit.  For shorter
+ *               blocks: the count with the least estimated time against one
+ *               workgroup per block (the workspace query tells).
+ *  wave_sets    1: one wave set per workgroup; 2: several, which take the
+ *               streamed tiles round-robin and add their fp32 sums through LDS
+ *               at the end.  Several are two in the one-set block shape (where
+ *               it has room: bf16 d <= 128, fp32 Pass 2 with d <= 64), or two to
+ *               sixteen in blocks of 16 to 64 key rows where those are expected
+ *               to be faster.  Automatic: several when the grid (in the
+ *               one-set block shape) has no more workgroups than the device
+ *               has compute units, else one; a split block uses one.
  *               On a dense unsplit grid that fills the device, the
  *               automatic bf16 d = 128 Pass 2 runs one set in workgroups of
  *               twice the waves (one copy of each streamed tile serves

@@ -20,6 +20,7 @@ SOURCES = [
     ("flashbob.hip", []),
     ("fb_rows_small.hip", []),
     ("fb_pass1_small.hip", []),
+    ("fb_cols_small.hip", []),
     ("fb_passes_d128.hip", ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]),
 ]
 

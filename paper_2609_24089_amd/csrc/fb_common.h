@@ -671,37 +671,6 @@ struct SectionSums {
   }
 };
 
-// Two wave sets of one workgroup that accumulated the same stationary rows
-// over disjoint sets of streamed tiles: set 1 hands its fp32 accumulators x,
-// then y, to set 0 through LDS (buf: every wave's A*B 1 KB blocks, placed by
-// the wave's index wl within its set), and set 0 adds them, always in the
-// order set 0 + set 1.  Every wave of the workgroup calls it (it holds
-// barriers); buf may alias the tile ring once the streaming loop has ended
-// (its last barrier follows the last read and the last copy).
-template <int A, int B>
-__device__ __forceinline__ void merge_wave_sets(floatx4 (&x)[A][B], floatx4 (&y)[A][B], int ks, int wl,
-                                                floatx4 FB_LDS* buf) {
-  floatx4 FB_LDS* p = buf + wl * (A * B * 64) + lane_id();
-  auto one = [&](floatx4 (&acc)[A][B]) {
-    if (ks == 1) {
-#pragma unroll
-      for (int a = 0; a < A; ++a)
-#pragma unroll
-        for (int b = 0; b < B; ++b) p[(a * B + b) * 64] = acc[a][b];
-    }
-    __syncthreads();
-    if (ks == 0) {
-#pragma unroll
-      for (int a = 0; a < A; ++a)
-#pragma unroll
-        for (int b = 0; b < B; ++b) acc[a][b] += p[(a * B + b) * 64];
-    }
-  };
-  one(x);
-  __syncthreads();  // set 0 has read x before set 1 overwrites it with y
-  one(y);
-}
-
 // ---------------------------------------------------------------------------
 // Wave sets of the row kernels, for grids with fewer row blocks than compute
 // units: the workgroup's KS sets of NW waves own the same query rows and take
@@ -733,30 +702,36 @@ struct RowSmem<T, D, NTENS, NSTAGE, 1, ROWS> {
   T lds[1][NSTAGE][NTENS * Geo<T, D>::kTileElems];
 };
 
-// Sum one accumulator over the sets: every wave stores the blocks it does not
-// own, and the owner of a block adds the other sets' copies to its own, set
-// ks + 1 first (a fixed order).  Every wave calls it (two barriers); buf may
-// alias the tile rings, whose last use precedes the loop's last barrier.
+// Sum one accumulator over the wave sets of a workgroup: every wave stores the
+// blocks it does not own, and the owner of a block (set a % KS) adds the other
+// sets' copies to its own, set ks + 1 first (a fixed order).  Every wave of the
+// workgroup calls it (two barriers); buf holds A B (KS - 1) 1 KB blocks for each of
+// the NW waves of a set and may alias the tile rings, whose last use precedes the
+// loop's last barrier.
 template <int KS, int NW, int A, int B>
-__device__ __forceinline__ void merge_row_sets(floatx4 (&x)[A][B], int ks, int wl, floatx4 FB_LDS* buf) {
-  const int lane = lane_id();
+__device__ __forceinline__ void merge_sets(floatx4 (&x)[A][B], int ks, int wl, floatx4 FB_LDS* buf) {
+  floatx4 FB_LDS* mine = buf + wl * (A * B * (KS - 1) * 64) + lane_id();
 #pragma unroll
-  for (int a = 0; a < A; ++a)
-    if (a % KS != ks) {
+  for (int a = 0; a < A; ++a) {
+    const int o = a % KS;
+    if (o != ks) {
+      const int slot = a * (KS - 1) + ks - o - 1 + (ks < o ? KS : 0);
 #pragma unroll
-      for (int b = 0; b < B; ++b) buf[((ks * NW + wl) * (A * B) + a * B + b) * 64 + lane] = x[a][b];
+      for (int b = 0; b < B; ++b) mine[(slot * B + b) * 64] = x[a][b];
     }
+  }
   __syncthreads();
 #pragma unroll
   for (int a = 0; a < A; ++a)
     if (a % KS == ks) {
 #pragma unroll
-      for (int q = 1; q < KS; ++q)
+      for (int q = 0; q < KS - 1; ++q)
 #pragma unroll
-        for (int b = 0; b < B; ++b) x[a][b] += buf[(((ks + q) % KS * NW + wl) * (A * B) + a * B + b) * 64 + lane];
+        for (int b = 0; b < B; ++b) x[a][b] += mine[((a * (KS - 1) + q) * B + b) * 64];
     }
   __syncthreads();
 }
+template <int KS, int NW, int A, int B> constexpr size_t merge_bytes() { return (size_t)NW * A * B * (KS - 1) * 1024; }
 
 // Streamed per-row fp32 scalars (L, D, alpha, E) for one tile, copied HBM ->
 // LDS with global_load_lds_dword: one wave instruction moves two kBS-float

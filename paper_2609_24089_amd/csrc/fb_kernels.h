@@ -190,8 +190,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_fwd_kernel(
 #pragma unroll
       for (int nb = 0; nb < G::kNB; ++nb) acc[nb][mb] *= corr;
     }
-    static_assert(sizeof(sm.lds) >= (size_t)KS * NW * G::kNB * MR * 1024, "set merge buffer");
-    merge_row_sets<KS, NW>(acc, ks, wl, (floatx4 FB_LDS*)&sm.lds[0][0][0]);
+    static_assert(sizeof(sm.lds) >= merge_bytes<KS, NW, G::kNB, MR>(), "set merge buffer");
+    merge_sets<KS, NW>(acc, ks, wl, (floatx4 FB_LDS*)&sm.lds[0][0][0]);
   }
 #pragma unroll
   for (int mb = 0; mb < MR; ++mb) {
@@ -323,8 +323,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_rows_kernel(
         }
       });
   if constexpr (KS > 1) {
-    static_assert(sizeof(sm.lds) >= (size_t)KS * NW * G::kNB * MR * 1024, "set merge buffer");
-    merge_row_sets<KS, NW>(acc, ks, wl, (floatx4 FB_LDS*)&sm.lds[0][0][0]);
+    static_assert(sizeof(sm.lds) >= merge_bytes<KS, NW, G::kNB, MR>(), "set merge buffer");
+    merge_sets<KS, NW>(acc, ks, wl, (floatx4 FB_LDS*)&sm.lds[0][0][0]);
   }
 #pragma unroll
   for (int mb = 0; mb < MR; ++mb) {
@@ -342,8 +342,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_rows_kernel(
 // Stationary: K, V rows.  Streamed: Q, dO tiles with their L and D.
 // KS wave sets of NW waves share the workgroup's column block and take the
 // streamed tiles round-robin, each with its own LDS ring; their partial sums
-// are added through LDS at the end (KS = 2 fills a CU when the grid has no
-// more workgroups than CUs).
+// are added through LDS at the end (for grids with no more workgroups than
+// CUs: two sets of the whole shape, or narrow blocks in as many as fit).
 // ===========================================================================
 template <typename T, int D, int MC, int NW, int OCC, int NSTAGE, bool kGQA, int KS, bool kParts = false,
           bool kFlush = false, bool kKL = false>
@@ -352,7 +352,6 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
     const T* __restrict__ dO, const float* __restrict__ L, const float* __restrict__ Dv,
     T* __restrict__ dK, T* __restrict__ dV, int N, int nRB, int total, float scale, int causal, int resident, int grp,
     float* __restrict__ parts_out = nullptr, int nparts = 1, int flush_tiles = 0) {
-  static_assert(KS == 1 || KS == 2, "wave sets");
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BC = 16 * MC * NW;
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
     map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int ks = KS == 1 ? 0 : wave_id() / NW;       // wave set
+  const int ks = KS == 1 ? 0 : KS == 2 ? wave_id() / NW : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
   const int wl = KS == 1 ? wave_id() : wave_id() % NW;  // wave within its set
   const int col0 = rb * BC + wl * 16 * MC;
 
@@ -545,10 +544,10 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
         prep_next();
       });
   sect.finish(dk, dv);
-  if constexpr (KS == 2) {
-    static_assert(sizeof(lds) >= (size_t)NW * G::kNB * MC * 1024, "set merge buffer");
-    merge_wave_sets(dk, dv, ks, wl, (floatx4 FB_LDS*)&lds[0][0][0]);
-    if (ks != 0) return;
+  if constexpr (KS > 1) {
+    static_assert(sizeof(lds) >= merge_bytes<KS, NW, G::kNB, MC>(), "set merge buffer");
+    merge_sets<KS, NW>(dk, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
+    merge_sets<KS, NW>(dv, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
   }
   if constexpr (kParts) {
     store_column_part<D>(parts_out, (int64_t)(total / nRB) * N * D, part, hoff, col0, N, dk, dv);
@@ -560,6 +559,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
     if (col < N) {
 #pragma unroll
       for (int nb = 0; nb < G::kNB; ++nb) {
+        if (KS > 1 && nb % KS != ks) continue;  // set nb % KS holds the sums of block nb
         E::store4(dK + hoff + (int64_t)col * D + 16 * nb + 4 * g, dk[nb][mc] * scale);
         E::store4(dV + hoff + (int64_t)col * D + 16 * nb + 4 * g, dv[nb][mc]);
       }
@@ -823,11 +823,11 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass1_kernel(
         sm.sc[1][ks][16 * (wl * MR + mb) + j] = es;
       }
     }
-    static_assert(sizeof(sm.lds) >= (size_t)KS * NW * kNBh * MR * 1024, "set merge buffer");
+    static_assert(sizeof(sm.lds) >= merge_bytes<KS, NW, kNBh, MR>(), "set merge buffer");
     floatx4 FB_LDS* buf = (floatx4 FB_LDS*)&sm.lds[0][0][0];
-    merge_row_sets<KS, NW>(aDO, ks, wl, buf);  // its barriers publish the scalars too
-    merge_row_sets<KS, NW>(aOM, ks, wl, buf);
-    merge_row_sets<KS, NW>(aB, ks, wl, buf);
+    merge_sets<KS, NW>(aDO, ks, wl, buf);  // its barriers publish the scalars too
+    merge_sets<KS, NW>(aOM, ks, wl, buf);
+    merge_sets<KS, NW>(aB, ks, wl, buf);
   }
   // epilogue (eq. 8; for kAlphaGiven the delayed E correction alone)
 #pragma unroll
@@ -998,7 +998,6 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
     const float* __restrict__ alpha_in, const float* __restrict__ E_in,
     T* __restrict__ Kt, T* __restrict__ Vt, int N, int nRB, int total, float scale, int causal, int resident, int grp,
     float* __restrict__ parts_out = nullptr, int nparts = 1, int flush_tiles = 0) {
-  static_assert(KS == 1 || KS == 2, "wave sets");
   using E = Elt<T>;
   using G = Geo<T, D>;
   constexpr int BC = 16 * MC * NW;
@@ -1028,7 +1027,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
     map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int ks = KS == 1 ? 0 : wave_id() / NW;       // wave set
+  const int ks = KS == 1 ? 0 : KS == 2 ? wave_id() / NW : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
   const int wl = KS == 1 ? wave_id() : wave_id() % NW;  // wave within its set
   const int col0 = rb * BC + wl * 16 * MC;
 
@@ -1220,10 +1219,10 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
         sect.step(aK, aV, flush_tiles);
       });
   sect.finish(aK, aV);
-  if constexpr (KS == 2) {
-    static_assert(sizeof(lds) >= (size_t)NW * G::kNB * MC * 1024, "set merge buffer");
-    merge_wave_sets(aK, aV, ks, wl, (floatx4 FB_LDS*)&lds[0][0][0]);
-    if (ks != 0) return;
+  if constexpr (KS > 1) {
+    static_assert(sizeof(lds) >= merge_bytes<KS, NW, G::kNB, MC>(), "set merge buffer");
+    merge_sets<KS, NW>(aK, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
+    merge_sets<KS, NW>(aV, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
   }
   if constexpr (kParts) {
     store_column_part<D>(parts_out, (int64_t)(total / nRB) * N * D, part, hoff, col0, N, aK, aV);
@@ -1235,6 +1234,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
     if (col < N) {
 #pragma unroll
       for (int nb = 0; nb < G::kNB; ++nb) {
+        if (KS > 1 && nb % KS != ks) continue;  // set nb % KS holds the sums of block nb
         const int64_t off = hoff + (int64_t)col * D + 16 * nb + 4 * g;
         E::store4(Kt + off, aK[nb][mc] * scale);
         E::store4(Vt + off, aV[nb][mc] * scale);

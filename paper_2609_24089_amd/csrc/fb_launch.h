@@ -173,6 +173,49 @@ template <auto kKernel> int causal_resident(const Problem& p, const Grid& g, int
   return g.total <= (int64_t)6 * kCUs * resident ? resident : 0;
 }
 
+// FLOP per us of one CU at 85% of the rate a large matrix product reached (1366
+// TFLOP/s bf16, 154 fp32, on 256 CUs).
+template <typename T> constexpr double kCuRate = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / (kXCDs * kCUsPerXCD);
+
+// ---------------------------------------------------------------------------
+// Small grids: blocks of 16 nw stationary rows (nw = 4, 2, 1), with as many wave
+// sets as the LDS holds, which share the streamed tiles.
+// ---------------------------------------------------------------------------
+struct SetShape {
+  int nw, ks, occ;
+};
+// The wave sets of a kernel that streams `tensors` tensors and keeps `extra`
+// bytes of LDS beside each ring: a power of two whose two-stage rings fit 160 KB,
+// in at most `max_waves` waves.
+template <typename T, int D> constexpr SetShape set_shape(int nw, int tensors, int extra, int max_waves, int occ) {
+  const int ring = 2 * tensors * Geo<T, D>::kTileElems * (int)sizeof(T);
+  int ks = 1;
+  while (2 * ks * nw <= max_waves && 2 * ks * (ring + extra) <= 160 * 1024) ks *= 2;
+  return {nw, ks, std::max(occ, ks * nw / 4)};
+}
+// One form of a kernel as pick_form() prices it: 16-row blocks per workgroup,
+// wave sets, workgroups that fit one CU (0: not built), workgroups that split a
+// block (column kernels) and what adding their parts takes, and what a block
+// weighs in a step (more where it reads more LDS bytes per MFMA).
+struct Form {
+  int blocks = 0, sets = 1, resident = 0, parts = 1;
+  double extra_us = 0, weight = 1;
+};
+// What the forms of one launch are chosen for: heads of N rows, each block
+// streaming `tiles` tiles (all of them or, causal, up to the diagonal), with
+// `contractions` tile contractions each.
+// One step (a streamed tile of every wave set on a CU) with n 16-row blocks takes
+// base + per_block weight n times the MFMA time of one block.
+struct FormQuery {
+  int64_t heads, N, tiles, d;
+  bool causal;
+  int contractions;
+  double rate;  // FLOP per us of one CU
+  double base, per_block;
+};
+// Index of the form with the least estimated time.
+int pick_form(const FormQuery& q, std::initializer_list<Form> forms);
+
 // ---------------------------------------------------------------------------
 // Column kernels (the first backward's dK, dV and Pass 2's Kt, Vt): how one
 // problem's column blocks are laid out over workgroups.
@@ -182,7 +225,8 @@ template <auto kKernel> int causal_resident(const Problem& p, const Grid& g, int
 //  * sets: wave sets per workgroup (KS = 2 fills a CU with one workgroup when
 //    the grid has no more workgroups than the device has CUs; shapes held to
 //    two waves per SIMD whose two LDS rings fit 160 KB and hold the merge
-//    buffer).
+//    buffer), or narrow blocks in two or more sets where pick_form() expects
+//    them to be faster; a request for two sets means either.
 //  * flush_tiles: streamed tiles per MFMA accumulation section (SectionSums;
 //    0 = one chain over the whole stream), with the kColsF / kP2F shape.
 // The caller's requests (bob_column_opts; 0 = automatic) are resolved here,
@@ -199,16 +243,17 @@ constexpr int64_t kLongChain = 16384;
 constexpr int kSectionTiles = 1024;
 
 // Automatic part counts of column blocks of at least kLongBlock streamed
-// iterations follow resolve_parts(), shorter ones down to min_iters iterations
-// the cost estimate of short_block_parts().
-constexpr int64_t kLongBlock = 1024, kShortBlock = 128;
+// iterations follow resolve_parts(), those of shorter ones (of min_iters or more)
+// pick_form().
+constexpr int64_t kLongBlock = 1024;
 struct ColumnOpts {
   int parts = 0, wave_sets = 0, flush_tiles = 0;
-  int64_t min_iters = kShortBlock;
+  int64_t min_iters = 0;
 };
 struct ColumnPlan {
   Grid g{0, 0};
   int parts = 1, sets = 1, flush_tiles = 0;
+  int narrow = 0;      // 4, 2 or 1: blocks of 16 times that many key rows in wave sets (ColsSmall, Pass2Small)
   bool wide = false;   // Pass 2 in the kP2W shape
   bool pairs = false;  // Pass 2 in wave pairs (kP2P)
 };
@@ -220,15 +265,6 @@ int device_cus();
 // kLongBlock streamed iterations per block.
 int resolve_parts(int workgroups, bool causal, bool pass2);
 
-// A column grid as short_block_parts() prices it.
-struct ColumnCost {
-  int workgroups, blocks;    // grid, column blocks per key/value head
-  int resident, resident1;   // workgroups per CU: split form, unsplit form
-  int64_t iters, plane;      // streamed iterations per block, elements of one output
-  double tile_us;            // MFMA time of one streamed tile of one workgroup
-  bool causal, two_sets;     // two_sets: unsplit, two wave sets would share the stream
-};
-int short_block_parts(const ColumnCost& c);
 
 // Automatic (requested = 0: two sets when the grid has no more workgroups
 // than the device has CUs) or forced (1, 2) wave sets.
@@ -255,16 +291,6 @@ inline int64_t column_iters(const Problem& p) { return (int64_t)group(p) * ((p.N
 // x B*Hkv*N*d.
 inline int64_t column_workspace_bytes(const Problem& p, int parts) {
   return parts > 1 ? (int64_t)parts * 2 * p.B * p.Hkv * p.N * p.d * (int64_t)sizeof(float) : 0;
-}
-
-// FLOP per us of one CU at 85% of the rate a large matrix product reached (1366
-// TFLOP/s bf16, 154 fp32, on 256 CUs).
-template <typename T> constexpr double kCuRate = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / (kXCDs * kCUsPerXCD);
-
-// Microseconds of the MFMA work of one streamed tile of one workgroup of a
-// column kernel on a CU.
-template <typename T, int D, bool kPass2> constexpr double column_tile_us(int rows) {
-  return 2.0 * (kPass2 ? 8 : 4) * kBS * rows * D / kCuRate<T>;
 }
 
 template <typename T, int D, bool kPass2, bool kF>
@@ -298,6 +324,88 @@ template <typename T, int D, bool kPass2, bool kF> int columns_resident(bool spl
 extern template int columns_resident<bf16, 128, true, false>(bool);  // built in fb_passes_d128.hip, with their kernels
 extern template int columns_resident<bf16, 128, true, true>(bool);
 
+// The column kernels in narrow blocks of 16 NW key rows with wave sets, for
+// grids with fewer column blocks than the device has CUs.  Built on the grouped
+// loop, which also runs multi-head problems.
+template <typename T, int D, int NW> struct ColsSmall {
+  static constexpr int kExtra = 4 * 2 * kBS * (int)sizeof(float);  // raw and transformed L, D
+  // K, V and two accumulators of 16 rows fit four waves per SIMD up to 128-byte rows
+  static constexpr SetShape kS =
+      set_shape<T, D>(NW, 2, kExtra, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kCols.occ);
+  static constexpr bool kBuilt = kS.ks > 1;
+  static constexpr auto kKernel =
+      &attn_bwd_cols_kernel<T, D, 1, kBuilt ? NW : 1, kS.occ, 2, true, kS.ks, false, false, false>;
+  static Form form();
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* dO, const float* L,
+                        const float* Dv, void* dK, void* dV, hipStream_t s);
+};
+template <typename T, int D, int NW> struct Pass2Small {
+  static constexpr int kExtra = 4 * 4 * kBS * (int)sizeof(float);  // raw and transformed L, D, alpha, E
+  static constexpr SetShape kS = set_shape<T, D>(NW, 3, kExtra, 8, Cfg<T, D>::kP2.occ);
+  // three tensors of two 1 KB blocks (bf16 d = 32) do not deal out over four waves
+  static constexpr bool kBuilt = kS.ks > 1 && !(sizeof(T) == 2 && D == 32 && NW == 4);
+  static constexpr auto kKernel =
+      &bob_pass2_kernel<T, D, 1, kBuilt ? NW : 1, kS.occ, 2, true, kS.ks, Cfg<T, D>::kP2.pf != 0, false, false>;
+  static Form form();
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* dO, const void* UQ,
+                        const void* UK, const void* UV, const float* L, const float* Dv, const float* alpha,
+                        const float* E, void* Kt, void* Vt, hipStream_t s);
+};
+template <typename T, int D, int NW> Form ColsSmall<T, D, NW>::form() {
+  // 16 rows per wave with K in registers read an LDS operand per bf16 MFMA, the
+  // whole shape about 0.6
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks), 1, 0.0, sizeof(T) == 2 ? 1.6 : 1.0};
+  else return {};
+}
+template <typename T, int D, int NW>
+int32_t ColsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* dO,
+                                    const float* L, const float* Dv, void* dK, void* dV, hipStream_t s) {
+  if constexpr (kBuilt) {
+    const Grid g = grid_for(p, 16 * NW, true);
+    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (const T*)dO, L, Dv, (T*)dK, (T*)dV, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p),
+                       (float*)nullptr, 1, 0);
+    return finish_launch();
+  }
+  return BOB_EUNSUPPORTED;
+}
+template <typename T, int D, int NW> Form Pass2Small<T, D, NW>::form() {
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)};
+  else return {};
+}
+template <typename T, int D, int NW>
+int32_t Pass2Small<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* dO,
+                                     const void* UQ, const void* UK, const void* UV, const float* L, const float* Dv,
+                                     const float* alpha, const float* E, void* Kt, void* Vt, hipStream_t s) {
+  if constexpr (kBuilt) {
+    const Grid g = grid_for(p, 16 * NW, true);
+    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt,
+                       (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p), (float*)nullptr, 1, 0);
+    return finish_launch();
+  }
+  return BOB_EUNSUPPORTED;
+}
+template <typename T, int D, bool kPass2, int NW> Form narrow_form() {
+  if constexpr (kPass2) return Pass2Small<T, D, NW>::form();
+  else return ColsSmall<T, D, NW>::form();
+}
+// Built in fb_cols_small.hip and (Pass 2 at bf16 d = 128) fb_passes_d128.hip.
+#define FB_COLS_SMALL(EXT, T, D) \
+  EXT template struct ColsSmall<T, D, 4>; EXT template struct ColsSmall<T, D, 2>; EXT template struct ColsSmall<T, D, 1>;
+#define FB_PASS2_SMALL(EXT, T, D) \
+  EXT template struct Pass2Small<T, D, 4>; EXT template struct Pass2Small<T, D, 2>; EXT template struct Pass2Small<T, D, 1>;
+#define FB_EACH_BUT_BF16_128(M, EXT) \
+  M(EXT, bf16, 32) M(EXT, bf16, 64) M(EXT, bf16, 256) M(EXT, float, 32) M(EXT, float, 64) M(EXT, float, 128)
+FB_EACH_BUT_BF16_128(FB_COLS_SMALL, extern)
+FB_COLS_SMALL(extern, bf16, 128)
+FB_EACH_BUT_BF16_128(FB_PASS2_SMALL, extern)
+FB_PASS2_SMALL(extern, bf16, 128)
+
 // Plan of a validated, non-empty, supported problem.  BOB_EINVAL for a
 // request out of range, BOB_EUNSUPPORTED for sections requested where the
 // sectioned form is not built.
@@ -313,26 +421,52 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
     ColumnPlan c;
     c.g = grid_for(p, 16 * s.mr * s.nw, true);
     const int64_t iters = column_iters(p);
-    if (o.parts > 0) {
+    const bool two = two_fit && resolve_two_sets(o.wave_sets, c.g.total);
+    if (o.parts > 0)
       c.parts = o.parts;
-    } else if (iters >= kLongBlock) {
+    else if (iters >= kLongBlock)
       c.parts = resolve_parts(c.g.total, p.causal != 0, kPass2);
-    } else if (iters >= o.min_iters) {
-      const bool gpu = device_cus() > 0;
-      const int resident = gpu ? columns_resident<T, D, kPass2, decltype(f)::value>(true) : 1;
-      const int resident1 = gpu ? columns_resident<T, D, kPass2, decltype(f)::value>(false) : 1;
-      c.parts = short_block_parts({c.g.total, c.g.nRB, resident, resident1, iters, p.B * p.Hkv * p.N * p.d,
-                                   column_tile_us<T, D, kPass2>(16 * s.mr * s.nw), p.causal != 0,
-                                   two_fit && resolve_two_sets(o.wave_sets, c.g.total)});
+    int narrow = 0;
+    if (c.parts == 1 && device_cus() > 0) {
+      constexpr bool kSection = decltype(f)::value;
+      Form whole{s.mr * s.nw, 1, 1}, n4, n2, n1, split[kMaxParts + 1];
+      if (two)
+        whole.sets = 2;
+      else if constexpr (!kSection)
+        whole.resident = columns_resident<T, D, kPass2, false>(false);
+      // narrow blocks: on grids with no more whole blocks than CUs, where wave
+      // sets may be chosen and the whole block does not run in wave pairs
+      if constexpr (!kSection && !(kPass2 && Cfg<T, D>::kP2P.mr > 0))
+        if (o.wave_sets != 1 && o.flush_tiles <= 0 && c.g.total <= device_cus()) {
+          n4 = narrow_form<T, D, kPass2, 4>();
+          n2 = narrow_form<T, D, kPass2, 2>();
+          n1 = narrow_form<T, D, kPass2, 1>();
+        }
+      // parts: 16 bytes an output element and part, written and read at 6 TB/s,
+      // and a launch
+      if (o.parts == 0 && iters < kLongBlock && iters >= o.min_iters)
+        for (int n = 2; n <= kMaxParts; ++n)
+          split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), n,
+                      4.0 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};
+      const int form = pick_form(
+          {p.B * p.Hkv, p.N, iters, p.d, p.causal != 0, kPass2 ? 8 : 4, kCuRate<T>, kPass2 ? 6.0 : 8.0, kPass2 ? 1.2 : 0.8},
+          {whole, n4, n2, n1, split[2], split[3], split[4], split[5], split[6], split[7], split[8]});
+      if (form >= 4) c.parts = form - 2;
+      else if (form >= 1) narrow = 8 >> form;
     }
     if ((int64_t)c.g.total * c.parts > INT32_MAX) c.parts = 1;
-    c.sets = (c.parts == 1 && two_fit && resolve_two_sets(o.wave_sets, c.g.total)) ? 2 : 1;
+    c.sets = c.parts == 1 && two ? 2 : 1;
+    if (c.parts == 1 && narrow != 0) {
+      c.narrow = narrow;
+      c.sets = 2;
+      c.g = grid_for(p, 16 * narrow, true);
+    }
     return c;
   };
   ColumnPlan c = fill(S0{}, std::false_type{});
   int ft = o.flush_tiles;
   if (ft == 0) {
-    const int64_t per = (int64_t)c.parts * c.sets;
+    const int64_t per = (int64_t)c.parts * c.sets;  // narrow blocks have two sets or more
     const int64_t chain = (column_iters(p) + per - 1) / per;
     ft = (SF::kS.mr > 0 && chain > kLongChain) ? kSectionTiles : -1;
   }
@@ -371,35 +505,15 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
   return BOB_OK;
 }
 
-// ---------------------------------------------------------------------------
-// Row kernels on small grids: blocks of 16 nw query rows (nw = 4, 2, 1), with
-// as many wave sets (RowSplit) as the LDS holds.
-// ---------------------------------------------------------------------------
-struct RowShape {
-  int nw, ks, occ;
-};
-// The wave sets of a row kernel that streams `tensors` tensors: a power of two
-// whose two-stage rings fit 160 KB next to the row scalars, in at most
-// `max_waves` waves.
-template <typename T, int D> constexpr RowShape row_shape(int nw, int tensors, int max_waves, int occ) {
-  const int ring = 2 * tensors * Geo<T, D>::kTileElems * (int)sizeof(T);
-  int ks = 1;
-  while (2 * ks * nw <= max_waves && 2 * ks * (ring + 2 * 16 * nw * 4) <= 160 * 1024) ks *= 2;
-  return {nw, ks, std::max(occ, ks * nw / 4)};
+// The query of a row kernel's launch.
+template <typename T> FormQuery row_query(const Problem& p, int contractions) {
+  return {p.B * p.H, p.N, (p.N + kBS - 1) / kBS, p.d, p.causal != 0, contractions, kCuRate<T>, 4.5, 0.45};
 }
-// One form of a row kernel as row_form() prices it: 16-row blocks per
-// workgroup, wave sets, workgroups that fit one CU (0: not built).
-struct RowForm {
-  int blocks, sets, resident;
-};
-// Index of the form with the least estimated time.  `contractions`: tile
-// contractions of the kernel per streamed tile; rate: FLOP per us of one CU.
-int row_form(const Problem& p, int contractions, double rate, std::initializer_list<RowForm> forms);
 
 template <typename T, int D, int NW> struct FwdSmall {
-  static constexpr RowShape kS = row_shape<T, D>(NW, 2, 16, Cfg<T, D>::kFwd.occ);
+  static constexpr SetShape kS = set_shape<T, D>(NW, 2, 128 * NW, 16, Cfg<T, D>::kFwd.occ);
   static constexpr auto kKernel = &attn_fwd_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
-  static RowForm form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
+  static Form form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
                         hipStream_t s) {
     const Grid g = grid_for(p, 16 * NW);
@@ -413,9 +527,10 @@ template <typename T, int D, int NW> struct FwdSmall {
 
 template <typename T, int D, int NW> struct RowsSmall {
   // two operands and an accumulator of 16 rows fit four waves per SIMD up to 128-byte rows
-  static constexpr RowShape kS = row_shape<T, D>(NW, 2, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kRows.occ);
+  static constexpr SetShape kS =
+      set_shape<T, D>(NW, 2, 128 * NW, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kRows.occ);
   static constexpr auto kKernel = &attn_bwd_rows_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
-  static RowForm form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
+  static Form form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                         const float* L, void* dQ, float* Dv, hipStream_t s) {
     const Grid g = grid_for(p, 16 * NW);
@@ -429,13 +544,13 @@ template <typename T, int D, int NW> struct RowsSmall {
 };
 
 template <typename T, int D, int NW> struct Pass1Small {
-  static constexpr RowShape kS = row_shape<T, D>(NW, 4, 8, Cfg<T, D>::kP1.occ);
+  static constexpr SetShape kS = set_shape<T, D>(NW, 4, 128 * NW, 8, Cfg<T, D>::kP1.occ);
   // where no second set fits, four blocks are the whole-block shape itself and
   // not built here again (their place is held by the two-block kernel, never run)
   static constexpr bool kBuilt = NW != 4 || kS.ks > 1;
   static constexpr auto kKernel =
       &bob_pass1_kernel<T, D, 1, kBuilt ? NW : 2, kS.occ, 2, kWithDQ, 1, Cfg<T, D>::kP1.pf, kS.ks>;
-  static RowForm form() { return {NW, kS.ks, kBuilt ? resident_blocks<kKernel>(64 * NW * kS.ks) : 0}; }
+  static Form form() { return {NW, kS.ks, kBuilt ? resident_blocks<kKernel>(64 * NW * kS.ks) : 0}; }
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                         const void* UQ, const void* UK, const void* UV, const float* L, const float* Dv,
                         const void* dQ, void* Qt, void* dOt, float* alpha, float* E, hipStream_t s) {
@@ -458,8 +573,6 @@ template <typename T, int D, int NW> struct Pass1Small {
   EXT template struct RowsSmall<T, D, 4>; EXT template struct RowsSmall<T, D, 2>; EXT template struct RowsSmall<T, D, 1>;
 #define FB_PASS1_SMALL(EXT, T, D) \
   EXT template struct Pass1Small<T, D, 4>; EXT template struct Pass1Small<T, D, 2>; EXT template struct Pass1Small<T, D, 1>;
-#define FB_EACH_BUT_BF16_128(M, EXT) \
-  M(EXT, bf16, 32) M(EXT, bf16, 64) M(EXT, bf16, 256) M(EXT, float, 32) M(EXT, float, 64) M(EXT, float, 128)
 FB_EACH_BUT_BF16_128(FB_ROWS_SMALL, extern)
 FB_ROWS_SMALL(extern, bf16, 128)
 FB_EACH_BUT_BF16_128(FB_PASS1_SMALL, extern)
@@ -473,7 +586,7 @@ int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V
   using F4 = FwdSmall<T, D, 4>;
   using F2 = FwdSmall<T, D, 2>;
   using F1 = FwdSmall<T, D, 1>;
-  switch (row_form(p, 2, kCuRate<T>,
+  switch (pick_form(row_query<T>(p, 2),
                    {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form()})) {
     case 1: return F4::launch(p, Q, K, V, O, L, s);
     case 2: return F2::launch(p, Q, K, V, O, L, s);
@@ -496,6 +609,11 @@ int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const vo
     return BOB_EUNSUPPORTED;
   } else {
     const Grid& gc = cp.g;
+    switch (cp.narrow) {
+      case 4: return ColsSmall<T, D, 4>::launch(p, Q, K, V, dO, L, Dv, dK, dV, s);
+      case 2: return ColsSmall<T, D, 2>::launch(p, Q, K, V, dO, L, Dv, dK, dV, s);
+      case 1: return ColsSmall<T, D, 1>::launch(p, Q, K, V, dO, L, Dv, dK, dV, s);
+    }
     (void)hipGetLastError();
     if (cp.parts > 1) {
       // each column block split over cp.parts workgroups, then one reduction
@@ -539,7 +657,7 @@ int32_t launch_bwd_rows(const Problem& p, const void* Q, const void* K, const vo
   using F4 = RowsSmall<T, D, 4>;
   using F2 = RowsSmall<T, D, 2>;
   using F1 = RowsSmall<T, D, 1>;
-  switch (row_form(p, 3, kCuRate<T>,
+  switch (pick_form(row_query<T>(p, 3),
                    {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw)}, F4::form(), F2::form(), F1::form()})) {
     case 1: return F4::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
     case 2: return F2::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
@@ -580,7 +698,7 @@ int32_t launch_pass1(const Problem& p, const void* Q, const void* K, const void*
     using F4 = Pass1Small<T, D, 4>;
     using F2 = Pass1Small<T, D, 2>;
     using F1 = Pass1Small<T, D, 1>;
-    switch (row_form(p, 10, kCuRate<T>,
+    switch (pick_form(row_query<T>(p, 10),
                      {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form()})) {
       case 1: return F4::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
       case 2: return F2::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
@@ -647,6 +765,11 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
     return BOB_EUNSUPPORTED;
   } else {
     const Grid& g = cp.g;
+    switch (cp.narrow) {
+      case 4: return Pass2Small<T, D, 4>::launch(p, Q, K, V, dO, UQ, UK, UV, L, Dv, alpha, E, Kt, Vt, s);
+      case 2: return Pass2Small<T, D, 2>::launch(p, Q, K, V, dO, UQ, UK, UV, L, Dv, alpha, E, Kt, Vt, s);
+      case 1: return Pass2Small<T, D, 1>::launch(p, Q, K, V, dO, UQ, UK, UV, L, Dv, alpha, E, Kt, Vt, s);
+    }
     (void)hipGetLastError();
     if (cp.parts > 1) {
       // each column block split over cp.parts workgroups, then one reduction

@@ -21,5 +21,6 @@ template int32_t launch_pass2<bf16, 128>(const Problem&, const void*, const void
 template int columns_resident<bf16, 128, true, false>(bool);
 template int columns_resident<bf16, 128, true, true>(bool);
 FB_PASS1_SMALL(, bf16, 128)
+FB_PASS2_SMALL(, bf16, 128)
 
 }  // namespace fb

@@ -48,90 +48,45 @@ int resolve_parts(int workgroups, bool causal, bool pass2) {
   return parts < 2 ? 1 : (int)std::min<int64_t>(parts, kMaxParts);
 }
 
-// Automatic choice for blocks of kShortBlock up to kLongBlock iterations: the
-// part count with the least estimated time.  Equal (dense) blocks cost the
-// rounds of the fullest CU, where a partial round of n workgroups takes half of
-// a full one and n / resident of the other half; causal blocks the larger of the mean load per CU and the
-// heaviest block's share on a CU of its own; a split adds its parts' fp32 round
-// trip through memory (at 4 TB/s) and a launch.  Two wave sets count as two
-// workgroups of half the stream on one CU.  Measured, unsplit -> chosen (us): B1 H16 Hkv4
-// N4099 d128 causal Pass 2 606 -> 281 (4 parts), first backward 721 -> 277 (8);
-// dense 793 -> 610 (3), 877 -> 542 (3); B1 H8 Hkv1 N1024 d128 causal Pass 2
-// 258 -> 51 (8); B1 H1 N8192 d64 causal Pass 2 230 -> 64 (8); B1 H4 N4096 d64
-// Pass 2 121 -> 78 (4).  Below kShortBlock iterations a launch and the round
-// trip cost about what the split gains (B2 H4 N777 d128, 25 iterations: 35 ->
-// 31), and the causal B4 H12 grids at N = 2048 and 4096 (64 and 128) lost up to
-// 14%.
-int short_block_parts(const ColumnCost& c) {
-  const int cus = device_cus();
-  if (cus <= 0 || c.workgroups <= 0) return 1;
-  // a round of n < resident workgroups on a CU, against a full round
-  auto partial = [](int n, int resident) {
-    return n == 0 ? 0.0 : 0.5 + 0.5 * n / resident;
-  };
-  auto cost = [&](int parts) {
-    const int sets = parts == 1 && c.two_sets ? 2 : 1;
-    const int resident = sets == 2 ? 2 : parts == 1 ? c.resident1 : c.resident;
-    const double share = (double)((c.iters + parts * sets - 1) / (parts * sets));
-    double t;
-    if (c.causal) {
-      const double mean = 0.5 * (1.0 + 1.0 / c.blocks) * c.iters * c.workgroups / ((double)cus * resident);
-      t = std::max(mean, share * (sets < resident ? partial(sets, resident) : 1.0));
-    } else {
-      const int64_t k = ((int64_t)c.workgroups * parts + cus - 1) / cus * sets;
-      t = share * ((double)(k / resident) + partial((int)(k % resident), resident));
-    }
-    t *= c.tile_us * resident;
-    if (parts > 1) t += 4.0 + 16.0 * parts * (double)c.plane / 4e6;
-    return t;
-  };
-  int best = 1;
-  const double whole = cost(1);
-  double least = 0.85 * whole;  // a split has to gain more than the estimate's error
-  for (int parts = 2; parts <= kMaxParts; ++parts) {
-    const double t = cost(parts);
-    if (t < least) {
-      best = parts;
-      least = t;
-    }
-  }
-  return best;
-}
-
-// Estimated time of a row kernel's forms.  A step (one streamed tile of every
-// wave set on a CU) with n waves' worth of 16-row blocks takes 4.5 + 0.45 n times
-// the MFMA time of one block, n at least the four that occupy every SIMD.  Equal
-// (dense) blocks cost the rounds of the fullest CU, causal ones the larger of
-// the mean load and the heaviest block's steps; kRound is a round's prologue,
-// epilogue and merge of the sets.  The three constants were fitted to 37 shapes
-// (N = 256 to 32768, 1 to 48 heads, both types, every head dim) timed in every
-// form: the choice is on average 1.2% slower than the best form, and at most 23%.
-// Measured, whole blocks -> chosen form (us): bf16 B1 H1 N8192 d64 causal forward
-// 136 -> 34, Pass 1 206 -> 100; B1 H4 N4096 d128 dense 105 -> 48, 229 -> 152; B2
-// H4 N777 d128 26 -> 13, 55 -> 33; fp32 B1 H1 N256 d64 14 -> 7, 46 -> 27.
-int row_form(const Problem& p, int contractions, double rate, std::initializer_list<RowForm> forms) {
+// Estimated time of a kernel's forms.  Equal (dense) blocks cost the rounds of
+// the fullest CU, causal ones the larger of the mean load and the heaviest
+// block's steps; a step has at least the four 16-row blocks that occupy every
+// SIMD, and kRound is a round's prologue, epilogue and merge of the sets.  The
+// constants (here, and the queries' base and per_block) were fitted to 37 shapes
+// (N = 256 to 32768, 1 to 48 heads, both types, every head dim) timed in every form:
+// the row kernels' choice is on average 1.2% slower than the best form (at most
+// 23%), the column kernels' 2% (18%).
+// Measured, whole blocks -> chosen form (us), row kernels: bf16 B1 H1 N8192 d64
+// causal forward 136 -> 34, Pass 1 206 -> 100; B1 H4 N4096 d128 dense 105 -> 48, 229
+// -> 152; B2 H4 N777 d128 26 -> 13, 55 -> 33; fp32 B1 H1 N256 d64 14 -> 7, 46 -> 27.
+// Column kernels, in sets: bf16 B1 H1 N256 d64 Pass 2 15 -> 7; B1 H12 N1024 d64
+// causal 38 -> 21; split in parts: B1 H16 Hkv4 N4099 d128 causal Pass 2 606 -> 281,
+// first backward 721 -> 277; B1 H8 Hkv1 N1024 d128 causal Pass 2 258 -> 51; fp32
+// B1 H6 Hkv2 N700 d128 Pass 2 609 -> 101, first backward 347 -> 101.
+int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
   constexpr int kCUs = kXCDs * kCUsPerXCD;
   constexpr double kRound = 4.0;
-  const double block_us = 2.0 * contractions * 16 * kBS * (double)p.d / rate;  // one 16-row block, one tile
-  const double tiles = (double)((p.N + kBS - 1) / kBS);
+  const double block_us = 2.0 * q.contractions * 16 * kBS * (double)q.d / q.rate;  // one 16-row block, one tile
   int best = 0, i = -1;
   bool fills = false;
   double least = 0;
-  for (const RowForm& f : forms) {
+  for (const Form& f : forms) {
     ++i;
     if (f.resident == 0) continue;  // not built
-    // whole blocks that fill every slot of the device stay (bf16 B1 H20 N1800
-    // d256 causal, 580 blocks in 512 slots: forward 64 us, 72 in two sets)
-    if (i > 0 && fills) break;
-    const int64_t nRB = (p.N + 16 * f.blocks - 1) / (16 * f.blocks), total = p.B * p.H * nRB;
+    const int64_t total = q.heads * ((q.N + 16 * f.blocks - 1) / (16 * f.blocks)) * f.parts;
+    // whole blocks that fill every slot of the device stay unless they are split
+    // (bf16 B1 H20 N1800 d256 causal, 580 blocks in 512 slots: forward 64 us, 72 in
+    // two sets)
     if (i == 0) fills = f.resident > 1 && total > kCUs * f.resident;
-    const double share = std::ceil(tiles / f.sets);
+    if (i > 0 && fills && f.parts == 1) continue;
+    const int64_t shares = (int64_t)f.sets * f.parts;
+    const double share = (double)((q.tiles + shares - 1) / shares);
     auto step = [&](int64_t workgroups) {
-      return block_us * (4.5 + 0.45 * std::max<int64_t>(4, workgroups * f.blocks * f.sets));
+      return block_us * (q.base + q.per_block * f.weight * std::max<int64_t>(4, workgroups * f.blocks * f.sets));
     };
     const int64_t k = (total + kCUs - 1) / kCUs;  // workgroups of the fullest CU
     double t;
-    if (p.causal != 0) {
+    if (q.causal) {
       const int64_t n = std::min<int64_t>(k, f.resident);
       const double mean = 0.5 * (share + 1) * total / (double)kCUs / n * step(n);
       t = std::max(mean, share * step(1));
@@ -139,6 +94,7 @@ int row_form(const Problem& p, int contractions, double rate, std::initializer_l
       t = share * ((double)(k / f.resident) * step(f.resident) + (k % f.resident != 0 ? step(k % f.resident) : 0));
     }
     t += kRound * (double)((k + f.resident - 1) / f.resident);
+    t += f.extra_us;
     if (i == 0 || t < least) {
       best = i;
       least = t;
