@@ -83,22 +83,33 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_fwd_kernel(
   // path find the tile's row maxima, move the reference of rows that grew by
   // more than 2^8, rescale their output accumulators and row sums, and form
   // p again.  `mode` 2 masks invalid entries (exponent -inf, p = 0).
+  // One check for all row blocks, so that their exponentials form one straight
+  // run of instructions.
   auto softmax_step = [&](int s0, int mode) {
+    float p[MR][8], ls[MR];
+    bool grown = false;
+    floatx4 e[MR][2];
 #pragma unroll
-    for (int mb = 0; mb < MR; ++mb) {
-      floatx4 e[2];
+    for (int mb = 0; mb < MR; ++mb)
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) e[sb][r] = __builtin_fmaf(s[sb][mb][r], c, -mrun[mb]);
-      if (mode == 2) mask_tile1<true>(e, s0, row0 + 16 * mb + j, N, causal != 0);
-      float p[8], ls = 0.f;
+        for (int r = 0; r < 4; ++r) e[mb][sb][r] = __builtin_fmaf(s[sb][mb][r], c, -mrun[mb]);
+    if (mode == 2) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        p[i] = fast_exp2(e[i >> 2][i & 3]);
-        ls += p[i];
-      }
-      if (__builtin_amdgcn_ballot_w64(!(ls <= kRescaleP)) != 0) {
+      for (int mb = 0; mb < MR; ++mb) mask_tile1<true>(e[mb], s0, row0 + 16 * mb + j, N, causal != 0);
+    }
+#pragma unroll
+    for (int mb = 0; mb < MR; ++mb) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[mb][i] = fast_exp2(e[mb][i >> 2][i & 3]);
+      ls[mb] = ((p[mb][0] + p[mb][1]) + (p[mb][2] + p[mb][3])) + ((p[mb][4] + p[mb][5]) + (p[mb][6] + p[mb][7]));
+      grown |= !(ls[mb] <= kRescaleP);
+    }
+    if (__builtin_amdgcn_ballot_w64(grown) != 0) {
+#pragma unroll
+      for (int mb = 0; mb < MR; ++mb) {
+        if (__builtin_amdgcn_ballot_w64(!(ls[mb] <= kRescaleP)) == 0) continue;
         // some row grew: tile maxima of the valid entries (in log2 units)
         floatx4 x[2];
 #pragma unroll
@@ -116,16 +127,19 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_fwd_kernel(
 #pragma unroll
           for (int nb = 0; nb < G::kNB; ++nb) acc[nb][mb] *= corr;
         }
-        ls = 0.f;
+        ls[mb] = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          p[i] = fast_exp2(x[i >> 2][i & 3] - mrun[mb]);
-          ls += p[i];
+          p[mb][i] = fast_exp2(x[i >> 2][i & 3] - mrun[mb]);
+          ls[mb] += p[mb][i];
         }
       }
-      lsum[mb] += ls;
+    }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pf[mb].set(i, p[i]);
+    for (int mb = 0; mb < MR; ++mb) {
+      lsum[mb] += ls[mb];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pf[mb].set(i, p[mb][i]);
     }
   };
 
@@ -139,7 +153,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_fwd_kernel(
       [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
         const int s0 = sp.tile(it) * kBS;
-        const int mode = sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0;
+        const int mode = __builtin_amdgcn_readfirstlane(
+            sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0);
         if (mode == 0) return;
         const T FB_LDS* Ks = (const T FB_LDS*)sm.lds[ks][st];
         const T FB_LDS* Vs = Ks + G::kTileElems;

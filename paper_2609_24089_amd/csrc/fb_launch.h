@@ -45,13 +45,13 @@ template <> struct Cfg<bf16, 32> {
   static constexpr Shape kColsF{2, 4, 2, 2}, kP2F{2, 2, 2, 2}, kP2W = kNoForm, kP2P = kNoForm;
 };
 template <> struct Cfg<bf16, 64> {
-  static constexpr Shape kFwd{2, 4, 2, 2}, kRows{2, 4, 2, 2}, kCols{2, 4, 2, 2, 1, 0, 1};
+  static constexpr Shape kFwd{2, 4, 4, 2}, kRows{2, 4, 2, 2}, kCols{2, 4, 2, 2, 1, 0, 1};
   static constexpr Shape kP1{1, 4, 2, 2}, kP1Six{1, 4, 2, 2}, kP2{2, 4, 2, 2};
   static constexpr Shape kAlpha{2, 4, 2, 2};
   static constexpr Shape kColsF{1, 4, 2, 2}, kP2F{1, 4, 3, 2}, kP2W = kNoForm, kP2P = kNoForm;
 };
 template <> struct Cfg<bf16, 128> {
-  static constexpr Shape kFwd{2, 4, 2, 2}, kRows{2, 4, 2, 2}, kCols{2, 4, 2, 2, 1, 0, 1};
+  static constexpr Shape kFwd{2, 4, 3, 2}, kRows{2, 4, 2, 2}, kCols{2, 4, 2, 2, 1, 0, 1};
   static constexpr Shape kP1{1, 8, 2, 2, 1, 1}, kP1Six{1, 4, 1, 2}, kP2{1, 4, 2, 2, 1, 1};
   static constexpr Shape kAlpha{2, 4, 2, 2};
   static constexpr Shape kColsF{1, 4, 2, 2}, kP2F{1, 4, 1, 2, 1, 1}, kP2W{1, 8, 2, 2, 1, 1}, kP2P = kNoForm;
@@ -525,6 +525,48 @@ template <typename T, int D, int NW> struct FwdSmall {
   }
 };
 
+// The whole block shape (32 rows per wave) in two wave sets, for grids that leave
+// a CU's slots empty or, causal, its last blocks alone.  Forward, whole -> two
+// sets (us): bf16 B2 H8 N4096 d64 93 -> 81, B1 H16 N4096 d64 causal 73 -> 54, B1
+// H8 N4096 d128 93 -> 79, B1 H1 N65536 d64 1489 -> 1215.
+template <typename T, int D> struct FwdWide {
+  static constexpr Shape kS = Cfg<T, D>::kFwd;
+  static constexpr bool kBuilt = kS.mr == 2;
+  static constexpr auto kKernel = &attn_fwd_kernel<T, D, kS.mr, kS.nw, kBuilt ? kS.occ : 1, kS.st, kBuilt ? 2 : 1>;
+  static Form form() {
+    return {kS.mr * kS.nw, 2, kBuilt ? resident_blocks<kKernel>(128 * kS.nw) : 0};
+  }
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
+                        hipStream_t s) {
+    if (!kBuilt) return BOB_EUNSUPPORTED;
+    const Grid g = grid_for(p, 16 * kS.mr * kS.nw);
+    const int res = causal_resident<kKernel>(p, g, 128 * kS.nw);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(128 * kS.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (T*)O,
+                       L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
+    return finish_launch();
+  }
+};
+template <typename T, int D> struct RowsWide {
+  static constexpr Shape kS = Cfg<T, D>::kRows;
+  static constexpr bool kBuilt = kS.mr == 2;
+  static constexpr auto kKernel = &attn_bwd_rows_kernel<T, D, kS.mr, kS.nw, kBuilt ? kS.occ : 1, kS.st, kBuilt ? 2 : 1>;
+  static Form form() {
+    return {kS.mr * kS.nw, 2, kBuilt ? resident_blocks<kKernel>(128 * kS.nw) : 0};
+  }
+  static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
+                        const float* L, void* dQ, float* Dv, hipStream_t s) {
+    if (!kBuilt) return BOB_EUNSUPPORTED;
+    const Grid g = grid_for(p, 16 * kS.mr * kS.nw);
+    const int res = causal_resident<kKernel>(p, g, 128 * kS.nw);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(128 * kS.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
+                       group(p));
+    return finish_launch();
+  }
+};
+
 template <typename T, int D, int NW> struct RowsSmall {
   // two operands and an accumulator of 16 rows fit four waves per SIMD up to 128-byte rows
   static constexpr SetShape kS =
@@ -569,6 +611,7 @@ template <typename T, int D, int NW> struct Pass1Small {
 // Built in fb_rows_small.hip, fb_pass1_small.hip and (Pass 1 at bf16 d = 128)
 // fb_passes_d128.hip.
 #define FB_ROWS_SMALL(EXT, T, D) \
+  EXT template struct FwdWide<T, D>; EXT template struct RowsWide<T, D>; \
   EXT template struct FwdSmall<T, D, 4>; EXT template struct FwdSmall<T, D, 2>; EXT template struct FwdSmall<T, D, 1>; \
   EXT template struct RowsSmall<T, D, 4>; EXT template struct RowsSmall<T, D, 2>; EXT template struct RowsSmall<T, D, 1>;
 #define FB_PASS1_SMALL(EXT, T, D) \
@@ -587,10 +630,12 @@ int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V
   using F2 = FwdSmall<T, D, 2>;
   using F1 = FwdSmall<T, D, 1>;
   switch (pick_form(row_query<T>(p, 2),
-                   {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form()})) {
+                   {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form(),
+                    FwdWide<T, D>::form()})) {
     case 1: return F4::launch(p, Q, K, V, O, L, s);
     case 2: return F2::launch(p, Q, K, V, O, L, s);
     case 3: return F1::launch(p, Q, K, V, O, L, s);
+    case 4: return FwdWide<T, D>::launch(p, Q, K, V, O, L, s);
   }
   const Grid g = grid_for(p, 16 * c.mr * c.nw);
   const int res = causal_resident<kernel>(p, g, 64 * c.nw);
@@ -658,10 +703,12 @@ int32_t launch_bwd_rows(const Problem& p, const void* Q, const void* K, const vo
   using F2 = RowsSmall<T, D, 2>;
   using F1 = RowsSmall<T, D, 1>;
   switch (pick_form(row_query<T>(p, 3),
-                   {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw)}, F4::form(), F2::form(), F1::form()})) {
+                   {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw)}, F4::form(), F2::form(), F1::form(),
+                    RowsWide<T, D>::form()})) {
     case 1: return F4::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
     case 2: return F2::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
     case 3: return F1::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+    case 4: return RowsWide<T, D>::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
   }
   const Grid gr = grid_for(p, 16 * cr.mr * cr.nw);
   const int res = causal_resident<rows>(p, gr, 64 * cr.nw);
