@@ -350,6 +350,10 @@ constexpr int tile_loads() {
 // therefore costs no vector address arithmetic, and rows at or past N read
 // as zeros by the buffer's range check (finite data that every kernel masks
 // out).
+// (m0 is reserved to the compiler, which sets it before each use of its own; the
+// opaque copies name it as clobbered.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <typename T, int D, int NW, int NTENS>
 struct TileCopy {
   using G = Geo<T, D>;
@@ -373,16 +377,34 @@ struct TileCopy {
   }
   __device__ __forceinline__ int block(int i) const { return kAllTensors ? w + i * NW : w % G::kBlocks; }
 
+  // kOpaque issues the copies through inline assembly, outside the compiler's
+  // count of outstanding loads: it otherwise waits for all of them before the
+  // first transposed LDS read of the tile (which may alias them for all it knows),
+  // and its scheduler moves that read to the top of the tile.  With two or more
+  // waves per SIMD at different tiles that wait is hidden; the wave sets of a small
+  // grid, one wave per SIMD or all at one barrier, stood through the copy's latency
+  // on every tile.  The loop's own waits (wait_copies) then order the copies.
+  template <bool kOpaque = false>
   __device__ __forceinline__ void issue(const T* const (&src)[NTENS], T FB_LDS* dst, int s0, int N) const {
     // bytes from row s0 to the end of the tile or of the matrix (< 2^31)
     const int bytes = min(N - s0, kBS) * kRowBytes;
     auto one = [&](const T* base, int t, int i) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource type exists for the device target only
-      const __amdgpu_buffer_rsrc_t rs =
-          __builtin_amdgcn_make_buffer_rsrc((void*)(base + (int64_t)s0 * D), (short)0, bytes, 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rs, (__attribute__((address_space(3))) void*)(dst + t * G::kTileElems + block(i) * kBlockElems), 16,
-          off[i], 0, 0, 0);
+      T FB_LDS* const to = dst + t * G::kTileElems + block(i) * kBlockElems;
+      if constexpr (kOpaque) {
+        // the same resource as below, in scalar registers (every part is wave-uniform)
+        const uint64_t at = (uint64_t)(base + (int64_t)s0 * D);
+        const u32x4 rs = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at),
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) & 0xffffu,
+                          (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+        const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)__builtin_bit_cast(uint32_t, to));
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :: "s"(m), "v"(off[i]), "s"(rs) : "memory", "m0");
+      } else {
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void*)(base + (int64_t)s0 * D), (short)0, bytes, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)to, 16, off[i], 0, 0, 0);
+      }
 #endif
     };
     if constexpr (kAllTensors) {
@@ -408,11 +430,21 @@ struct TileCopy {
   }
 };
 
+#pragma clang diagnostic pop
+
 // Wait until at most N vector-memory loads of this wave are outstanding
 // (loads complete in issue order for this count).
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
+
+// Wait for every copy of this wave.  With kOpaque copies the compiler has to see
+// the wait: it would otherwise repeat it inside the loop for its own loads from
+// before the loop.
+template <bool kOpaque> __device__ __forceinline__ void wait_copies() {
+  if constexpr (kOpaque) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters at their maxima
+  wait_vm<0>();
+}
 
 // Set the exponents of invalid (masked) tile entries to -inf, so exp2 gives
 // P = 0 there.  x[sb][m][r] belongs to streamed row s0 + 16 sb + 4 (l >> 4) + r
@@ -461,14 +493,14 @@ __device__ __forceinline__ void mask_tile1(floatx4 (&x)[2], int s0, int t, int N
 // see is a compile-time constant: LDS addresses become loop-invariant
 // registers plus immediate offsets, and the copy's LDS destination a
 // constant.
-template <int NSTAGE, int LT, class Issue, class Body>
+template <int NSTAGE, int LT, bool kOpaque = false, class Issue, class Body>
 __device__ __forceinline__ void stream_loop(int it_begin, int it_end, Issue&& issue, Body&& body) {
   static_assert(NSTAGE == 2 || NSTAGE == 3, "pipeline depth");
   const int n = it_end - it_begin;
 #pragma unroll
   for (int st = 0; st < NSTAGE - 1; ++st)
     if (st < n) issue(it_begin + st, st);
-  wait_vm<0>();
+  wait_copies<kOpaque>();
   __syncthreads();
   // iteration k consumes stage k % NSTAGE and refills stage (k - 1) % NSTAGE
   auto step = [&](int k, auto cur) {
@@ -482,7 +514,7 @@ __device__ __forceinline__ void stream_loop(int it_begin, int it_end, Issue&& is
     if (NSTAGE == 3 && nx < n)
       wait_vm<LT>();
     else
-      wait_vm<0>();
+      wait_copies<kOpaque>();
     __syncthreads();
   };
   for (int k = 0; k < n; k += NSTAGE) {
@@ -505,7 +537,7 @@ __device__ __forceinline__ void stream_loop(int it_begin, int it_end, Issue&& is
 // body(tile, matrix stage, transformed slot, prep_next).  Two stages: the
 // loop is unrolled by two, so every stage and slot index is a compile-time
 // constant (as in stream_loop).
-template <int NSTAGE, int LT, int LS, class IssueS, class IssueM, class Prep, class Body>
+template <int NSTAGE, int LT, int LS, bool kOpaque = false, class IssueS, class IssueM, class Prep, class Body>
 __device__ __forceinline__ void stream_loop_rs(int it_begin, int it_end, bool owner, IssueS&& issue_s,
                                                IssueM&& issue_m, Prep&& prep, Body&& body) {
   static_assert(NSTAGE == 2, "the column kernels run a two-stage ring");
@@ -515,7 +547,7 @@ __device__ __forceinline__ void stream_loop_rs(int it_begin, int it_end, bool ow
     if (owner && 1 < n) issue_s(it_begin + 1, 1);
     issue_m(it_begin, 0);
   }
-  wait_vm<0>();
+  wait_copies<kOpaque>();
   if (owner && n > 0) prep(it_begin, 0, 0);
   __syncthreads();
   // iteration k: matrices in stage k % 2 (the next tile's go to the other
@@ -533,7 +565,7 @@ __device__ __forceinline__ void stream_loop_rs(int it_begin, int it_end, bool ow
     });
     // the next tile's matrices (and, on the owner, the scalars of the tile
     // after) must have landed
-    wait_vm<0>();
+    wait_copies<kOpaque>();
     __syncthreads();
   };
   for (int k = 0; k < n; k += 2) {
@@ -740,13 +772,24 @@ template <int KS, int NW, int A, int B> constexpr size_t merge_bytes() { return 
 // pointers are passed by value so that the per-lane choice is a register
 // select (an indexed pointer array would go through scratch memory and force
 // a full vmcnt wait).  Asynchronous like the tile copy.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <bool kOpaque = false>
 __device__ __forceinline__ void issue_scalar_pair(float FB_LDS* dst, const float* a, const float* b, int s0, int N) {
   static_assert(kBS == 32, "two 32-float vectors per wave instruction");
   const int l = lane_id();
   const int idx = min(s0 + (l & 31), N - 1);
   const float* p = (l < 32 ? a : b) + idx;
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
-                                   (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+  if constexpr (kOpaque) {  // as TileCopy::issue
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)__builtin_bit_cast(uint32_t, dst));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(m), "v"(p) : "memory", "m0");
+#endif
+  } else {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                     (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+  }
 }
+#pragma clang diagnostic pop
 
 }  // namespace fb

@@ -20,9 +20,9 @@
 // head row block; column kernels one per key/value head column block, and
 // stream the grp query heads of that key/value head one after another, so
 // their key-side outputs sum over the group with no atomics.  On grids with
-// no more workgroups than CUs a column workgroup holds two wave sets that
-// split those streamed tiles and add their partial sums through LDS.  The
-// kParts forms split a column block over several workgroups instead, each
+// no more workgroups than CUs a workgroup (of a column or row kernel) holds
+// several wave sets (KS) that split the streamed tiles and add their partial
+// sums through LDS.  The kParts forms split a column block over several workgroups instead, each
 // storing fp32 partial sums to a caller's workspace that
 // bob_column_parts_reduce_kernel adds (small or causal grids).
 #pragma once
@@ -148,9 +148,9 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_fwd_kernel(
   const int it_end = causal ? min(nT, (min(rb * BR + BR, N) - 1) / kBS + 1) : nT;
   const RowSplit<KS> sp{ks, it_end};
   const TileCopy<T, D, NW, 2> copy(wl);
-  stream_loop<NSTAGE, tile_loads<T, D, NW, 2>()>(
+  stream_loop<NSTAGE, tile_loads<T, D, NW, 2>(), (KS > 1)>(
       0, sp.iterations(),
-      [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
+      [&](int it, int st) { copy.template issue<(KS > 1)>(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
         const int s0 = sp.tile(it) * kBS;
         const int mode = __builtin_amdgcn_readfirstlane(
@@ -293,9 +293,9 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_rows_kernel(
   const int it_end = causal ? min(nT, (min(rb * BR + BR, N) - 1) / kBS + 1) : nT;
   const RowSplit<KS> sp{ks, it_end};
   const TileCopy<T, D, NW, 2> copy(wl);
-  stream_loop<NSTAGE, tile_loads<T, D, NW, 2>()>(
+  stream_loop<NSTAGE, tile_loads<T, D, NW, 2>(), (KS > 1)>(
       0, sp.iterations(),
-      [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
+      [&](int it, int st) { copy.template issue<(KS > 1)>(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
         const int s0 = sp.tile(it) * kBS;
         const int mode = sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0;
@@ -455,16 +455,16 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
   const int nTh = nT - it_begin;
   const StreamSplit<kGQA, KS, kParts> sp{it_begin, nTh, kGQA ? grp * nTh : nTh, ks, bh, grp, part, nparts};
   const TileCopy<T, D, NW, 2> copy(wl);
-  stream_loop_rs<NSTAGE, tile_loads<T, D, NW, 2>(), 1>(
+  stream_loop_rs<NSTAGE, tile_loads<T, D, NW, 2>(), 1, (KS > 1)>(
       sp.begin(), sp.end(nT), __builtin_amdgcn_readfirstlane(wl) == 0,
       [&](int it, int rs) {
         const int64_t qs = (int64_t)sp.qhead(it) * N;
-        issue_scalar_pair((float FB_LDS*)rawsc[ks][rs], L + qs, Dv + qs, sp.tile(it) * kBS, N);
+        issue_scalar_pair<(KS > 1)>((float FB_LDS*)rawsc[ks][rs], L + qs, Dv + qs, sp.tile(it) * kBS, N);
       },
       [&](int it, int st) {
         const int64_t qo = (int64_t)sp.qhead(it) * N * D;
         const T* const src[2] = {Q + qo, dO + qo};
-        copy.issue(src, (T FB_LDS*)lds[ks][st], sp.tile(it) * kBS, N);
+        copy.template issue<(KS > 1)>(src, (T FB_LDS*)lds[ks][st], sp.tile(it) * kBS, N);
       },
       [&](int it, int rs, int ts) {
         (void)it;
@@ -804,9 +804,9 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass1_kernel(
   const int it_end = causal ? min(nT, (min(rb * BR + BR, N) - 1) / kBS + 1) : nT;
   const RowSplit<KS> sp{ks, it_end};
   const TileCopy<T, D, NW, 4> copy(wl);
-  stream_loop<NSTAGE, tile_loads<T, D, NW, 4>()>(
+  stream_loop<NSTAGE, tile_loads<T, D, NW, 4>(), (KS > 1)>(
       0, sp.iterations(),
-      [&](int it, int st) { copy.issue(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
+      [&](int it, int st) { copy.template issue<(KS > 1)>(src, (T FB_LDS*)sm.lds[ks][st], sp.tile(it) * kBS, N); },
       [&](int it, int st) {
         const int s0 = sp.tile(it) * kBS;
         const int mode = sp.live(it) ? tile_mode_rowmajor(s0, row0, row0 + 16 * MR - 1, N, causal != 0) : 0;
@@ -1099,18 +1099,18 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
   const int nTh = nT - it_begin;
   const StreamSplit<kGQA, KS, kParts> sp{it_begin, nTh, kGQA ? grp * nTh : nTh, ks, bh, grp, part, nparts};
   const TileCopy<T, D, NW, 3> copy(wl);
-  stream_loop_rs<NSTAGE, tile_loads<T, D, NW, 3>(), 2>(
+  stream_loop_rs<NSTAGE, tile_loads<T, D, NW, 3>(), 2, (KS > 1)>(
       sp.begin(), sp.end(nT), __builtin_amdgcn_readfirstlane(wl) == 0,
       [&](int it, int rs) {
         const int64_t qs = (int64_t)sp.qhead(it) * N;
         float FB_LDS* dst = (float FB_LDS*)rawsc[ks][rs];
-        issue_scalar_pair(dst, L + qs, Dv + qs, sp.tile(it) * kBS, N);
-        issue_scalar_pair(dst + 2 * kBS, alpha_in + qs, E_in + qs, sp.tile(it) * kBS, N);
+        issue_scalar_pair<(KS > 1)>(dst, L + qs, Dv + qs, sp.tile(it) * kBS, N);
+        issue_scalar_pair<(KS > 1)>(dst + 2 * kBS, alpha_in + qs, E_in + qs, sp.tile(it) * kBS, N);
       },
       [&](int it, int st) {
         const int64_t qo = (int64_t)sp.qhead(it) * N * D;
         const T* const src[3] = {Q + qo, UQ + qo, dO + qo};
-        copy.issue(src, (T FB_LDS*)lds[ks][st], sp.tile(it) * kBS, N);
+        copy.template issue<(KS > 1)>(src, (T FB_LDS*)lds[ks][st], sp.tile(it) * kBS, N);
       },
       [&](int it, int rs, int ts) {
         (void)it;
