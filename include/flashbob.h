@@ -35,8 +35,9 @@
  *          allocates no memory (the *_ws calls take their workspace from
  *          the caller) and keeps no state apart from the device address of
  *          the static scratch buffer of attn_bob_pass2_cols_gqa_noalloc:
- *          every choice it makes depends only on the arguments and on the
- *          current device's compute-unit count, so the entry points are
+ *          every choice it makes depends only on the arguments, on the
+ *          current device's compute-unit count and on how many workgroups of
+ *          a kernel fit a compute unit, so the entry points are
  *          thread-safe (two _noalloc calls that overlap on one device race
  *          on its scratch, see there).
  *          Outputs must not alias inputs.

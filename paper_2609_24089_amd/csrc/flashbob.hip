@@ -78,7 +78,7 @@ int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
     // (bf16 B1 H20 N1800 d256 causal, 580 blocks in 512 slots: forward 64 us, 72 in
     // two sets)
     if (i == 0) fills = f.resident > 1 && total > kCUs * f.resident;
-    if (i > 0 && fills && f.parts == 1) continue;
+    if (i > 0 && ((fills && f.parts == 1) || total > INT32_MAX)) continue;
     const int64_t shares = (int64_t)f.sets * f.parts;
     const double share = (double)((q.tiles + shares - 1) / shares);
     auto step = [&](int64_t workgroups) {
