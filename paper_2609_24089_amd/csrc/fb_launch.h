@@ -434,6 +434,13 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
         whole.sets = 2;
       else if constexpr (!kSection)
         whole.resident = columns_resident<T, D, kPass2, false>(false);
+      // the wide blocks that an unsplit dense Pass 2 runs in (below) take 0.94-0.97 of
+      // the narrow ones' time, so a split has that much more to gain (bf16 B1 H12 Hkv6
+      // N10099 d128: unsplit 2254 us, four parts 2482; B1 H16 Hkv8 N6000: two parts 1084)
+      if constexpr (!kSection && kPass2 && Cfg<T, D>::kP2W.mr > 0)
+        if (constexpr Shape w = Cfg<T, D>::kP2W; !two && o.wave_sets == 0 && !p.causal && o.flush_tiles <= 0 &&
+            grid_for(p, 16 * w.mr * w.nw, true).total >= device_cus())
+          whole = {w.mr * w.nw, 1, 1, 1, 0.0, 0.92};
       // narrow blocks: on grids with no more whole blocks than CUs, where wave
       // sets may be chosen and the whole block does not run in wave pairs
       if constexpr (!kSection && !(kPass2 && Cfg<T, D>::kP2P.mr > 0))
