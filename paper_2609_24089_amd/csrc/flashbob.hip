@@ -94,6 +94,9 @@ int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
       t = share * ((double)(k / f.resident) * step(f.resident) + (k % f.resident != 0 ? step(k % f.resident) : 0));
     }
     t += kRound * (double)((k + f.resident - 1) / f.resident);
+    // equal blocks are split only for a clear gain: an estimated gain of a few percent
+    // was a loss (fp32 B1 H12 Hkv6 N5050 d64 Pass 2: 2481 us split, 2434 unsplit)
+    if (!q.causal && f.parts > 1) t *= 1.08;
     t += f.extra_us;
     if (i == 0 || t < least) {
       best = i;
