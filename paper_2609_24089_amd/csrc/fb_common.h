@@ -384,6 +384,11 @@ struct TileCopy {
   // waves per SIMD at different tiles that wait is hidden; the wave sets of a small
   // grid, one wave per SIMD or all at one barrier, stood through the copy's latency
   // on every tile.  The loop's own waits (wait_copies) then order the copies.
+  // A VMEM instruction may read an SGPR that a VALU instruction wrote (the resource's
+  // v_readfirstlane) five wait states later at the earliest, with no hardware interlock,
+  // and the compiler keeps no distance to a load inside inline assembly: the write of
+  // m0 and s_nop 3 are five wherever the register was written, and more than the one
+  // that the load needs after the write of m0.
   template <bool kOpaque = false>
   __device__ __forceinline__ void issue(const T* const (&src)[NTENS], T FB_LDS* dst, int s0, int N) const {
     // bytes from row s0 to the end of the tile or of the matrix (< 2^31)
@@ -398,7 +403,7 @@ struct TileCopy {
                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) & 0xffffu,
                           (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
         const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)__builtin_bit_cast(uint32_t, to));
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                      :: "s"(m), "v"(off[i]), "s"(rs) : "memory", "m0");
       } else {
         const __amdgpu_buffer_rsrc_t rs =

@@ -404,7 +404,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
     map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int ks = KS == 1 ? 0 : KS == 2 ? wave_id() / NW : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
   const int wl = KS == 1 ? wave_id() : wave_id() % NW;  // wave within its set
   const int col0 = rb * BC + wl * 16 * MC;
 
@@ -561,8 +561,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void attn_bwd_cols_kernel(
   sect.finish(dk, dv);
   if constexpr (KS > 1) {
     static_assert(sizeof(lds) >= merge_bytes<KS, NW, G::kNB, MC>(), "set merge buffer");
-    merge_sets<KS, NW>(dk, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
-    merge_sets<KS, NW>(dv, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
+    merge_sets<KS, NW>(dk, ks, wl, (floatx4 FB_LDS*)&lds[0][0][0]);
+    merge_sets<KS, NW>(dv, ks, wl, (floatx4 FB_LDS*)&lds[0][0][0]);
   }
   if constexpr (kParts) {
     store_column_part<D>(parts_out, (int64_t)(total / nRB) * N * D, part, hoff, col0, N, dk, dv);
@@ -1042,7 +1042,7 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
     map_block(nRB, total, bh, rb);
   const int64_t hoff = (int64_t)bh * N * D;
   const int l = lane_id(), g = l >> 4, j = l & 15;
-  const int ks = KS == 1 ? 0 : KS == 2 ? wave_id() / NW : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id() / NW);  // wave set
   const int wl = KS == 1 ? wave_id() : wave_id() % NW;  // wave within its set
   const int col0 = rb * BC + wl * 16 * MC;
 
@@ -1236,8 +1236,8 @@ __global__ __launch_bounds__(KS * NW * 64, OCC) void bob_pass2_kernel(
   sect.finish(aK, aV);
   if constexpr (KS > 1) {
     static_assert(sizeof(lds) >= merge_bytes<KS, NW, G::kNB, MC>(), "set merge buffer");
-    merge_sets<KS, NW>(aK, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
-    merge_sets<KS, NW>(aV, __builtin_amdgcn_readfirstlane(ks), wl, (floatx4 FB_LDS*)&lds[0][0][0]);
+    merge_sets<KS, NW>(aK, ks, wl, (floatx4 FB_LDS*)&lds[0][0][0]);
+    merge_sets<KS, NW>(aV, ks, wl, (floatx4 FB_LDS*)&lds[0][0][0]);
   }
   if constexpr (kParts) {
     store_column_part<D>(parts_out, (int64_t)(total / nRB) * N * D, part, hoff, col0, N, aK, aV);
