@@ -179,7 +179,11 @@ template <typename T> constexpr double kCuRate = (sizeof(T) == 2 ? 1366e6 : 154e
 
 // ---------------------------------------------------------------------------
 // Small grids: blocks of 16 nw stationary rows (nw = 4, 2, 1), with as many wave
-// sets as the LDS holds, which share the streamed tiles.
+// sets as the LDS holds, which share the streamed tiles.  The structs below name
+// their kernel in kernel() alone, which only form() and launch() call, and those are
+// defined out of class: a unit compiles the kernels of the structs that it
+// instantiates and no others (an address in a class-level constant compiled every
+// kernel in every unit).
 // ---------------------------------------------------------------------------
 struct SetShape {
   int nw, ks, occ;
@@ -333,8 +337,10 @@ template <typename T, int D, int NW> struct ColsSmall {
   static constexpr SetShape kS =
       set_shape<T, D>(NW, 2, kExtra, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kCols.occ);
   static constexpr bool kBuilt = kS.ks > 1;
-  static constexpr auto kKernel =
-      &attn_bwd_cols_kernel<T, D, 1, kBuilt ? NW : 1, kS.occ, 2, true, kS.ks, false, false, false>;
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt)
+      return &attn_bwd_cols_kernel<T, D, 1, NW, kS.occ, 2, true, kS.ks, false, false, false>;
+  }
   static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* dO, const float* L,
                         const float* Dv, void* dK, void* dV, hipStream_t s);
@@ -342,10 +348,15 @@ template <typename T, int D, int NW> struct ColsSmall {
 template <typename T, int D, int NW> struct Pass2Small {
   static constexpr int kExtra = 4 * 4 * kBS * (int)sizeof(float);  // raw and transformed L, D, alpha, E
   static constexpr SetShape kS = set_shape<T, D>(NW, 3, kExtra, 8, Cfg<T, D>::kP2.occ);
-  // three tensors of two 1 KB blocks (bf16 d = 32) do not deal out over four waves
-  static constexpr bool kBuilt = kS.ks > 1 && !(sizeof(T) == 2 && D == 32 && NW == 4);
-  static constexpr auto kKernel =
-      &bob_pass2_kernel<T, D, 1, kBuilt ? NW : 1, kS.occ, 2, true, kS.ks, Cfg<T, D>::kP2.pf != 0, false, false>;
+  // three tensors of two 1 KB blocks (bf16 d = 32) do not deal out over four waves;
+  // where four blocks in two sets are the whole shape's two sets, those run
+  static constexpr bool kSameAsWhole = Cfg<T, D>::kP2.mr == 1 && Cfg<T, D>::kP2.nw == NW && kS.ks == 2 &&
+                                       ColumnShape<T, D, true, false>::kTwoFit;
+  static constexpr bool kBuilt = kS.ks > 1 && !kSameAsWhole && !(sizeof(T) == 2 && D == 32 && NW == 4);
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt)
+      return &bob_pass2_kernel<T, D, 1, NW, kS.occ, 2, true, kS.ks, Cfg<T, D>::kP2.pf != 0, false, false>;
+  }
   static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* dO, const void* UQ,
                         const void* UK, const void* UV, const float* L, const float* Dv, const float* alpha,
@@ -354,7 +365,7 @@ template <typename T, int D, int NW> struct Pass2Small {
 template <typename T, int D, int NW> Form ColsSmall<T, D, NW>::form() {
   // 16 rows per wave with K in registers read an LDS operand per bf16 MFMA, the
   // whole shape about 0.6
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks), 1, 0.0, sizeof(T) == 2 ? 1.6 : 1.0};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 1, 0.0, sizeof(T) == 2 ? 1.6 : 1.0};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -362,9 +373,9 @@ int32_t ColsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void*
                                     const float* L, const float* Dv, void* dK, void* dV, hipStream_t s) {
   if constexpr (kBuilt) {
     const Grid g = grid_for(p, 16 * NW, true);
-    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
     (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                        (const T*)dO, L, Dv, (T*)dK, (T*)dV, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p),
                        (float*)nullptr, 1, 0);
     return finish_launch();
@@ -372,7 +383,7 @@ int32_t ColsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void*
   return BOB_EUNSUPPORTED;
 }
 template <typename T, int D, int NW> Form Pass2Small<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -381,9 +392,9 @@ int32_t Pass2Small<T, D, NW>::launch(const Problem& p, const void* Q, const void
                                      const float* alpha, const float* E, void* Kt, void* Vt, hipStream_t s) {
   if constexpr (kBuilt) {
     const Grid g = grid_for(p, 16 * NW, true);
-    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
     (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                        (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt,
                        (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p), (float*)nullptr, 1, 0);
     return finish_launch();
@@ -519,18 +530,24 @@ template <typename T> FormQuery row_query(const Problem& p, int contractions) {
 
 template <typename T, int D, int NW> struct FwdSmall {
   static constexpr SetShape kS = set_shape<T, D>(NW, 2, 128 * NW, 16, Cfg<T, D>::kFwd.occ);
-  static constexpr auto kKernel = &attn_fwd_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
-  static Form form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
+  static __host__ constexpr auto kernel() { return &attn_fwd_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>; }
+  static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
-                        hipStream_t s) {
-    const Grid g = grid_for(p, 16 * NW);
-    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
-                       (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
-    return finish_launch();
-  }
+                        hipStream_t s);
 };
+template <typename T, int D, int NW> Form FwdSmall<T, D, NW>::form() {
+  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+}
+template <typename T, int D, int NW>
+int32_t FwdSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
+                                   hipStream_t s) {
+  const Grid g = grid_for(p, 16 * NW);
+  const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                     (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
+  return finish_launch();
+}
 
 // The whole block shape (32 rows per wave) in two wave sets, for grids that leave
 // a CU's slots empty or, causal, its last blocks alone.  Forward, whole -> two
@@ -539,81 +556,117 @@ template <typename T, int D, int NW> struct FwdSmall {
 template <typename T, int D> struct FwdWide {
   static constexpr Shape kS = Cfg<T, D>::kFwd;
   static constexpr bool kBuilt = kS.mr == 2;
-  static constexpr auto kKernel = &attn_fwd_kernel<T, D, kS.mr, kS.nw, kBuilt ? kS.occ : 1, kS.st, kBuilt ? 2 : 1>;
-  static Form form() {
-    return {kS.mr * kS.nw, 2, kBuilt ? resident_blocks<kKernel>(128 * kS.nw) : 0};
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt) return &attn_fwd_kernel<T, D, kS.mr, kS.nw, kS.occ, kS.st, 2>;
   }
+  static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
-                        hipStream_t s) {
-    if (!kBuilt) return BOB_EUNSUPPORTED;
+                        hipStream_t s);
+};
+template <typename T, int D> Form FwdWide<T, D>::form() {
+  if constexpr (kBuilt) return {kS.mr * kS.nw, 2, resident_blocks<kernel()>(128 * kS.nw)};
+  else return {};
+}
+template <typename T, int D>
+int32_t FwdWide<T, D>::launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
+                              hipStream_t s) {
+  if constexpr (kBuilt) {
     const Grid g = grid_for(p, 16 * kS.mr * kS.nw);
-    const int res = causal_resident<kKernel>(p, g, 128 * kS.nw);
+    const int res = causal_resident<kernel()>(p, g, 128 * kS.nw);
     (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(128 * kS.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (T*)O,
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(128 * kS.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V, (T*)O,
                        L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
     return finish_launch();
   }
-};
+  return BOB_EUNSUPPORTED;
+}
 template <typename T, int D> struct RowsWide {
   static constexpr Shape kS = Cfg<T, D>::kRows;
   static constexpr bool kBuilt = kS.mr == 2;
-  static constexpr auto kKernel = &attn_bwd_rows_kernel<T, D, kS.mr, kS.nw, kBuilt ? kS.occ : 1, kS.st, kBuilt ? 2 : 1>;
-  static Form form() {
-    return {kS.mr * kS.nw, 2, kBuilt ? resident_blocks<kKernel>(128 * kS.nw) : 0};
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt) return &attn_bwd_rows_kernel<T, D, kS.mr, kS.nw, kS.occ, kS.st, 2>;
   }
+  static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
-                        const float* L, void* dQ, float* Dv, hipStream_t s) {
-    if (!kBuilt) return BOB_EUNSUPPORTED;
+                        const float* L, void* dQ, float* Dv, hipStream_t s);
+};
+template <typename T, int D> Form RowsWide<T, D>::form() {
+  if constexpr (kBuilt) return {kS.mr * kS.nw, 2, resident_blocks<kernel()>(128 * kS.nw)};
+  else return {};
+}
+template <typename T, int D>
+int32_t RowsWide<T, D>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
+                               const void* dO, const float* L, void* dQ, float* Dv, hipStream_t s) {
+  if constexpr (kBuilt) {
     const Grid g = grid_for(p, 16 * kS.mr * kS.nw);
-    const int res = causal_resident<kKernel>(p, g, 128 * kS.nw);
+    const int res = causal_resident<kernel()>(p, g, 128 * kS.nw);
     (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(128 * kS.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(128 * kS.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                        (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
                        group(p));
     return finish_launch();
   }
-};
+  return BOB_EUNSUPPORTED;
+}
 
 template <typename T, int D, int NW> struct RowsSmall {
   // two operands and an accumulator of 16 rows fit four waves per SIMD up to 128-byte rows
   static constexpr SetShape kS =
       set_shape<T, D>(NW, 2, 128 * NW, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kRows.occ);
-  static constexpr auto kKernel = &attn_bwd_rows_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
-  static Form form() { return {NW, kS.ks, resident_blocks<kKernel>(64 * NW * kS.ks)}; }
+  static __host__ constexpr auto kernel() { return &attn_bwd_rows_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>; }
+  static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
-                        const float* L, void* dQ, float* Dv, hipStream_t s) {
-    const Grid g = grid_for(p, 16 * NW);
-    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
-                       (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
-                       group(p));
-    return finish_launch();
-  }
+                        const float* L, void* dQ, float* Dv, hipStream_t s);
 };
+template <typename T, int D, int NW> Form RowsSmall<T, D, NW>::form() {
+  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+}
+template <typename T, int D, int NW>
+int32_t RowsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
+                                    const void* dO, const float* L, void* dQ, float* Dv, hipStream_t s) {
+  const Grid g = grid_for(p, 16 * NW);
+  const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                     (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
+                     group(p));
+  return finish_launch();
+}
 
 template <typename T, int D, int NW> struct Pass1Small {
   static constexpr SetShape kS = set_shape<T, D>(NW, 4, 128 * NW, 8, Cfg<T, D>::kP1.occ);
   // where no second set fits, four blocks are the whole-block shape itself and
-  // not built here again (their place is held by the two-block kernel, never run)
+  // not built here again
   static constexpr bool kBuilt = NW != 4 || kS.ks > 1;
-  static constexpr auto kKernel =
-      &bob_pass1_kernel<T, D, 1, kBuilt ? NW : 2, kS.occ, 2, kWithDQ, 1, Cfg<T, D>::kP1.pf, kS.ks>;
-  static Form form() { return {NW, kS.ks, kBuilt ? resident_blocks<kKernel>(64 * NW * kS.ks) : 0}; }
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt) return &bob_pass1_kernel<T, D, 1, NW, kS.occ, 2, kWithDQ, 1, Cfg<T, D>::kP1.pf, kS.ks>;
+  }
+  static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                         const void* UQ, const void* UK, const void* UV, const float* L, const float* Dv,
-                        const void* dQ, void* Qt, void* dOt, float* alpha, float* E, hipStream_t s) {
-    if (!kBuilt) return BOB_EUNSUPPORTED;
+                        const void* dQ, void* Qt, void* dOt, float* alpha, float* E, hipStream_t s);
+};
+template <typename T, int D, int NW> Form Pass1Small<T, D, NW>::form() {
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+  else return {};
+}
+template <typename T, int D, int NW>
+int32_t Pass1Small<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
+                                     const void* dO, const void* UQ, const void* UK, const void* UV, const float* L,
+                                     const float* Dv, const void* dQ, void* Qt, void* dOt, float* alpha, float* E,
+                                     hipStream_t s) {
+  if constexpr (kBuilt) {
     const Grid g = grid_for(p, 16 * NW);
-    const int res = causal_resident<kKernel>(p, g, 64 * NW * kS.ks);
+    const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
     (void)hipGetLastError();
-    hipLaunchKernelGGL(kKernel, dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                        (const T*)O, (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, (const T*)dQ,
                        (const float*)nullptr, (T*)Qt, (T*)dOt, alpha, E, (int)p.N, g.nRB, g.total, p.scale, p.causal,
                        res, group(p));
     return finish_launch();
   }
-};
+  return BOB_EUNSUPPORTED;
+}
 
 // Built in fb_rows_small.hip, fb_pass1_small.hip and (Pass 1 at bf16 d = 128)
 // fb_passes_d128.hip.
@@ -652,6 +705,21 @@ int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V
   return finish_launch();
 }
 
+// Adds the parts of a split column kernel: x times p.scale and y times y_scale.
+// Launched right after the split kernel, whose launch error finish_launch() here
+// still sees.  Built in flashbob.hip.
+template <typename T>
+int32_t launch_parts_reduce(const Problem& p, int parts, const float* ws, float y_scale, void* x, void* y,
+                            hipStream_t s) {
+  const int64_t plane = p.B * p.Hkv * p.N * p.d;
+  const int blocks = (int)std::min<int64_t>((plane / 2 + 255) / 256, 4096);
+  hipLaunchKernelGGL((bob_column_parts_reduce_kernel<T>), dim3(blocks), dim3(256), 0, s, ws, parts, plane, p.scale,
+                     y_scale, (T*)x, (T*)y);
+  return finish_launch();
+}
+extern template int32_t launch_parts_reduce<bf16>(const Problem&, int, const float*, float, void*, void*, hipStream_t);
+extern template int32_t launch_parts_reduce<float>(const Problem&, int, const float*, float, void*, void*, hipStream_t);
+
 template <typename T, int D, bool kF>
 int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const void* V, const void* dO,
                         const float* L, const float* Dv, void* dK, void* dV, hipStream_t s, const ColumnPlan& cp,
@@ -672,11 +740,7 @@ int32_t launch_bwd_cols(const Problem& p, const void* Q, const void* K, const vo
       hipLaunchKernelGGL((parts_kernel<T, D, false, kF>()), dim3(gc.total * cp.parts), dim3(64 * cc.nw), 0, s, (const T*)Q, (const T*)K, (const T*)V,
                          (const T*)dO, L, Dv, (T*)dK, (T*)dV, (int)p.N, gc.nRB, gc.total, p.scale, p.causal,
                          0, group(p), parts_ws, cp.parts, cp.flush_tiles);
-      const int64_t plane = p.B * p.Hkv * p.N * p.d;
-      const int blocks = (int)std::min<int64_t>((plane / 2 + 255) / 256, 4096);
-      hipLaunchKernelGGL((bob_column_parts_reduce_kernel<T>), dim3(blocks), dim3(256), 0, s, (const float*)parts_ws,
-                         cp.parts, plane, p.scale, 1.0f, (T*)dK, (T*)dV);
-      return finish_launch();
+      return launch_parts_reduce<T>(p, cp.parts, parts_ws, 1.0f, dK, dV, s);
     }
     auto cols = [&](auto gqa, auto ks) {
       constexpr auto kernel = &attn_bwd_cols_kernel<T, D, cc.mr, cc.nw, cc.occ, cc.st, decltype(gqa)::value,
@@ -831,11 +895,7 @@ int32_t launch_pass2_form(const Problem& p, const void* Q, const void* K, const 
                          (const T*)dO, (const T*)UQ, (const T*)UK, (const T*)UV, L, Dv, alpha, E, (T*)Kt, (T*)Vt,
                          (int)p.N, g.nRB, g.total, p.scale, p.causal, 0, group(p), parts_ws, cp.parts,
                          cp.flush_tiles);
-      const int64_t plane = p.B * p.Hkv * p.N * p.d;
-      const int blocks = (int)std::min<int64_t>((plane / 2 + 255) / 256, 4096);
-      hipLaunchKernelGGL((bob_column_parts_reduce_kernel<T>), dim3(blocks), dim3(256), 0, s, (const float*)parts_ws,
-                         cp.parts, plane, p.scale, p.scale, (T*)Kt, (T*)Vt);
-      return finish_launch();
+      return launch_parts_reduce<T>(p, cp.parts, parts_ws, p.scale, Kt, Vt, s);
     }
     const bool gqa = group(p) != 1;
     if constexpr (!kF && Cfg<T, D>::kP2W.mr > 0) {

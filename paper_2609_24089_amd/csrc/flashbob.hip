@@ -7,6 +7,9 @@
 
 namespace fb {
 
+template int32_t launch_parts_reduce<bf16>(const Problem&, int, const float*, float, void*, void*, hipStream_t);
+template int32_t launch_parts_reduce<float>(const Problem&, int, const float*, float, void*, void*, hipStream_t);
+
 // Compute units of the current device, read from the runtime on every call
 // (the library keeps no state of its own).
 int device_cus() {
