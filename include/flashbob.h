@@ -92,7 +92,8 @@ typedef enum {
  *               dense Pass 2 grids smaller than the compute-unit count to 2
  *               per unit, the dense first backward to 8 per unit.  For shorter
  *               blocks: the count with the least estimated time against one
- *               workgroup per block (the workspace query tells).
+ *               workgroup per block (the workspace query tells), if wave_sets
+ *               is automatic too and the call brings the workspace; else one.
  *  wave_sets    1: one wave set per workgroup; 2: several, which take the
  *               streamed tiles round-robin and add their fp32 sums through LDS
  *               at the end.  Several are two in the one-set block shape (where
@@ -216,7 +217,9 @@ int32_t attn_bob_pass2_cols_gqa(int32_t dtype, int64_t B, int64_t H, int64_t Hkv
  *          must not be reused before the call's kernels have finished on
  *          `stream`.  When that size is 0 (the layout does not split) the
  *          workspace is ignored and may be NULL; otherwise a NULL,
- *          misaligned or too small workspace gives BOB_EINVAL.
+ *          misaligned or too small workspace gives BOB_EINVAL, but for
+ *          blocks of fewer than 1024 streamed tiles with parts automatic:
+ *          those then run unsplit.
  * A request out of range (parts outside 0..8, wave_sets outside 0..2,
  * flush_tiles below -1) gives BOB_EINVAL.  dQ and D of the first backward do
  * not depend on the layout. */
@@ -262,8 +265,9 @@ int32_t bob_column_layout(int32_t kernel, int32_t dtype, int64_t B, int64_t H, i
  *          process ends.  A split needs parts x 2 x B x Hkv x N x d x 4 bytes
  *          of it.  With parts automatic (opts NULL or opts->parts == 0) the
  *          call splits blocks of at least 1024 streamed tiles only, into the
- *          largest automatic part count that fits, or runs unsplit; a forced opts->parts whose split does not fit gives
- *          BOB_ESCRATCH before any launch.
+ *          largest automatic part count that fits, or runs unsplit; a forced
+ *          opts->parts whose split does not fit gives BOB_ESCRATCH before any
+ *          launch.
  *  races   every call on one device shares that device's scratch, which
  *          keeps the last call's contents (a split writes every element it
  *          later reads, so nothing needs clearing).  Two calls that overlap

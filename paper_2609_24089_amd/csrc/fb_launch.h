@@ -461,8 +461,8 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
           n1 = narrow_form<T, D, kPass2, 1>();
         }
       // parts: 16 bytes an output element and part, written and read at 6 TB/s,
-      // and a launch
-      if (o.parts == 0 && iters < kLongBlock && iters >= o.min_iters)
+      // and a launch; not where wave sets are asked for, which a split has none of
+      if (o.parts == 0 && o.wave_sets == 0 && iters < kLongBlock && iters >= o.min_iters)
         for (int n = 2; n <= kMaxParts; ++n)
           split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), n,
                       4.0 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};

@@ -148,11 +148,19 @@ static int32_t column_plan(const Problem& p, bool pass2, const ColumnOpts& o, Co
   FB_DISPATCH(p, plan_bwd, p, o, c);
 }
 
-// The workspace checks of a *_ws entry point for a plan that splits.
-static int32_t check_workspace(const Problem& p, const ColumnPlan& c, const void* ws, int64_t bytes) {
-  if (c.parts <= 1) return BOB_OK;
-  if (ws == nullptr || bytes < column_workspace_bytes(p, c.parts) || check_ptrs({ws}) != BOB_OK) return BOB_EINVAL;
-  return BOB_OK;
+// The plan of a column kernel whose parts go to the caller's workspace.  Automatic
+// parts of short blocks use it if it is there: those blocks run unsplit where a
+// caller brings none (or one that is too small), as they did before they were ever
+// split.  Any other split without its workspace is BOB_EINVAL.
+static int32_t ws_plan(const Problem& p, bool pass2, const ColumnOpts& o, const void* ws, int64_t bytes,
+                       ColumnPlan* c) {
+  auto fits = [&] { return c->parts <= 1 || (bytes >= column_workspace_bytes(p, c->parts) && aligned16(ws)); };
+  int32_t rc = column_plan(p, pass2, o, c);
+  if (rc != BOB_OK || fits()) return rc;
+  ColumnOpts long_only = o;
+  long_only.min_iters = kLongBlock;
+  if ((rc = column_plan(p, pass2, long_only, c)) != BOB_OK) return rc;
+  return fits() ? BOB_OK : BOB_EINVAL;
 }
 
 static int32_t run_bwd(const Problem& p, const ColumnOpts& o, const void* Q, const void* K, const void* V,
@@ -162,9 +170,8 @@ static int32_t run_bwd(const Problem& p, const ColumnOpts& o, const void* Q, con
   int32_t rc = check_problem(p, &empty);
   if (rc != BOB_OK) return rc;
   ColumnPlan c;
-  if ((rc = column_plan(p, false, o, &c)) != BOB_OK || empty) return rc;
+  if ((rc = ws_plan(p, false, o, ws, ws_bytes, &c)) != BOB_OK || empty) return rc;
   if ((rc = check_ptrs({Q, K, V, O, dO, L, dQ, dK, dV, D})) != BOB_OK) return rc;
-  if ((rc = check_workspace(p, c, ws, ws_bytes)) != BOB_OK) return rc;
   FB_DISPATCH(p, launch_bwd, p, Q, K, V, O, dO, L, dQ, dK, dV, D, (hipStream_t)stream, c, (float*)ws);
 }
 
@@ -176,9 +183,8 @@ static int32_t run_pass2(const Problem& p, const ColumnOpts& o, const void* Q, c
   int32_t rc = check_problem(p, &empty);
   if (rc != BOB_OK) return rc;
   ColumnPlan c;
-  if ((rc = column_plan(p, true, o, &c)) != BOB_OK || empty) return rc;
+  if ((rc = ws_plan(p, true, o, ws, ws_bytes, &c)) != BOB_OK || empty) return rc;
   if ((rc = check_ptrs({Q, K, V, dO, gdQ, gdK, gdV, L, D, alpha, E, Kt, Vt})) != BOB_OK) return rc;
-  if ((rc = check_workspace(p, c, ws, ws_bytes)) != BOB_OK) return rc;
   FB_DISPATCH(p, launch_pass2, p, Q, K, V, dO, gdQ, gdK, gdV, L, D, alpha, E, Kt, Vt, (hipStream_t)stream, c,
               (float*)ws);
 }

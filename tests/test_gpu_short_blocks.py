@@ -64,3 +64,44 @@ def test_splits_where_blocks_are_few():
         lay, nbytes = fb.column_layout(fb.BOB_COLUMNS_PASS2, dt, 1, H, Hkv, N, d, causal)
         say(f"[short blocks] H{H} Hkv{Hkv} N{N} d{d}: {lay}, {nbytes} bytes")
         assert lay.parts >= 4 and nbytes == lay.parts * 2 * Hkv * N * d * 4
+
+
+@pytest.mark.parametrize("dt,H,Hkv,N,d,causal", [("bf16", 8, 1, 1024, 128, True), ("f32", 6, 2, 700, 128, False)])
+def test_no_workspace_or_asked_wave_sets_run_unsplit(dt, H, Hkv, N, d, causal):
+    """Blocks whose automatic layout splits: a C caller without a workspace (or with
+    one that is too small or misaligned) gets the unsplit layout, and so does a
+    request for wave sets; a forced part count still needs its workspace."""
+    import ctypes
+    import paper_2609_24089_amd as fb
+    lib = fb.load_library()
+    code = fb.BOB_BF16 if dt == "bf16" else fb.BOB_F32
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    x = {k: v.cuda() for k, v in make_gqa_inputs(1, H, Hkv, N, d, dt, 271).items()}
+    scale, one = d ** -0.5, fb.ColumnOpts(1, 0, 0)
+    ref = fb.bob(*[x[n] for n in NAMES], scale, causal=causal, columns=one)
+    for kernel in (fb.BOB_COLUMNS_BWD, fb.BOB_COLUMNS_PASS2):
+        assert fb.column_layout(kernel, tdt, 1, H, Hkv, N, d, causal)[0].parts > 1
+        for sets in (1, 2):
+            asked = fb.column_layout(kernel, tdt, 1, H, Hkv, N, d, causal, fb.ColumnOpts(0, sets, 0))
+            assert asked[0].parts == 1 and asked[1] == 0
+            if sets == 1:
+                assert asked[0].wave_sets == 1
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    head = (code, 1, H, Hkv, N, d, ctypes.c_float(scale), int(causal))
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    small = torch.empty(64, dtype=torch.uint8, device="cuda")
+    large = torch.empty(8 * 2 * Hkv * N * d * 4 + 16, dtype=torch.uint8, device="cuda")
+    for ws, nbytes in ((None, 0), (p(small), 64), (ctypes.c_void_p(large.data_ptr() + 8), large.numel() - 8)):
+        Kt, Vt = torch.empty_like(x["K"]), torch.empty_like(x["K"])
+        mats = [p(x[n]) for n in ("Q", "K", "V", "dO", "UQ", "UK", "UV")] + [p(ref[n]) for n in ("L", "D", "alpha", "E")]
+        call = lambda o: lib.attn_bob_pass2_cols_gqa_ws(*head, *mats, p(Kt), p(Vt), o, ws, nbytes, stream)  # noqa: E731
+        assert call(None) == fb.BOB_OK
+        assert torch.equal(Kt, ref["Kt"]) and torch.equal(Vt, ref["Vt"])
+        assert call(ctypes.byref(fb.ColumnOpts(8, 0, 0))) == fb.BOB_EINVAL
+        outs = [torch.empty_like(x["Q"]), torch.empty_like(x["K"]), torch.empty_like(x["K"]), torch.empty_like(ref["D"])]
+        mats = [p(x[n]) for n in ("Q", "K", "V")] + [p(ref["O"]), p(x["dO"]), p(ref["L"])]
+        call = lambda o: lib.attn_bwd_gqa_ws(*head, *mats, *map(p, outs), o, ws, nbytes, stream)  # noqa: E731
+        assert call(None) == fb.BOB_OK
+        for got, k in zip(outs, ("dQ", "dK", "dV", "D")):
+            assert torch.equal(got, ref[k]), k
+        assert call(ctypes.byref(fb.ColumnOpts(8, 0, 0))) == fb.BOB_EINVAL
