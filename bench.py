@@ -53,8 +53,8 @@ NOMINAL_BOB_COEF = 38
 OTHER_CONFIGS = {"bf16_b2h8_n4096_d64": (20, 3), "bf16_b1h8_n65536_d64": (5, 1),
                  "bf16_b1h4_n262144_d64": (3, 1)}
 
-KERNEL_SOURCES = ["fb_common.h", "fb_kernels.h", "fb_launch.h", "flashbob.hip", "fb_passes_d128.hip", "fb_rows_small.hip",
-                  "fb_pass1_small.hip", "fb_cols_small.hip"]
+KERNEL_SOURCES = ["fb_common.h", "fb_forms.h", "fb_kernels.h", "fb_launch.h", "flashbob.hip", "fb_passes_d128.hip",
+                  "fb_rows_small.hip", "fb_pass1_small.hip", "fb_cols_small.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.json")
 PEAK_N_FILE = os.path.join(ROOT, "profiles", "peak_n.json")
 

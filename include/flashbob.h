@@ -33,11 +33,12 @@
  *  pointers  device pointers owned by the caller, 16-byte aligned, on the
  *          current HIP device (the kernels run there).  The library
  *          allocates no memory (the *_ws calls take their workspace from
- *          the caller) and keeps no state apart from the device address of
- *          the static scratch buffer of attn_bob_pass2_cols_gqa_noalloc:
- *          every choice it makes depends only on the arguments, on the
- *          current device's compute-unit count and on how many workgroups of
- *          a kernel fit a compute unit, so the entry points are
+ *          the caller) and keeps no state apart from constants that it
+ *          reads once: each device's compute-unit count, how many
+ *          workgroups of a kernel fit a compute unit, and the device
+ *          address of the static scratch buffer of
+ *          attn_bob_pass2_cols_gqa_noalloc.  Every choice it makes depends
+ *          only on the arguments and on these, so the entry points are
  *          thread-safe (two _noalloc calls that overlap on one device race
  *          on its scratch, see there).
  *          Outputs must not alias inputs.

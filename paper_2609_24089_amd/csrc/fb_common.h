@@ -30,6 +30,8 @@
 
 #include <type_traits>
 
+#include "fb_forms.h"
+
 namespace fb {
 
 typedef __bf16 bf16;
@@ -250,9 +252,6 @@ template <typename T, int D> struct Geo {
   }
 };
 
-constexpr int kXCDs = 8;
-constexpr int kCUsPerXCD = 32;
-
 // Map a workgroup to (head, row block).  Workgroups are dispatched round-robin
 // over the 8 XCDs; when the count allows it, consecutive logical blocks (which
 // stream the same head's tensors) are kept on one XCD so they share its L2.
@@ -268,7 +267,7 @@ __device__ __forceinline__ void map_block(int nRB, int total, int& bh, int& rb, 
 
 // The same under the causal mask on grids of a few rounds over the CUs
 // (`resident` workgroups of the kernel fit one CU; launches choose this order
-// by causal_resident()), where block rb's work grows with its tiles at or below
+// by balanced_order()), where block rb's work grows with its tiles at or below
 // the diagonal (`last_heavy`: the last block is the heaviest, as in the row
 // kernels; else the first, as in the column kernels).  Blocks are ranked
 // heaviest first over all heads, so that the dispatcher's refills end on the

@@ -11,6 +11,7 @@
 #include <initializer_list>
 
 #include "../../include/flashbob.h"
+#include "fb_forms.h"
 #include "fb_kernels.h"
 
 namespace fb {
@@ -146,6 +147,9 @@ inline Grid grid_for(const Problem& p, int rows_per_block, bool kv_heads = false
   return g;
 }
 
+// Compute units of the current device (0 if it cannot be read).
+int device_cus();
+
 // Workgroups of kKernel that fit one CU (1 if the runtime cannot tell), read
 // once per kernel: a property of its code object.
 template <auto kKernel> int resident_blocks(int threads) {
@@ -157,25 +161,18 @@ template <auto kKernel> int resident_blocks(int threads) {
   return resident;
 }
 
-// The `resident` argument of a kernel launch: the workgroups of kKernel that
-// fit one CU if the causal grid is to run in the balanced order
-// (map_block_causal), else 0 (heads one after another).  A grid of one round
-// has a CU for every block, and on grids of more than about six times the
-// resident blocks the refills balance the load by themselves while blocks of
-// one head in flight at a time share its streamed tiles in L2: measured bf16
-// B4 H12 N16384 d64 (24 and 48 rounds, 4 and 3 resident), the balanced order ran
-// Pass 1 5% and Pass 2 3% slower and the forward 2% faster; at N4096 (6 and 12
-// rounds) it ran Pass 1 6%, Pass 2 15% and the forward 24% faster.
+// The `resident` argument of a launch of kKernel (balanced_order()).
 template <auto kKernel> int causal_resident(const Problem& p, const Grid& g, int threads) {
-  constexpr int kCUs = kXCDs * kCUsPerXCD;
-  if (p.causal == 0 || g.total <= kCUs) return 0;
-  const int resident = resident_blocks<kKernel>(threads);
-  return g.total <= (int64_t)6 * kCUs * resident ? resident : 0;
+  return p.causal == 0 ? 0 : balanced_order(g.total, resident_blocks<kKernel>(threads), device_cus());
 }
 
-// FLOP per us of one CU at 85% of the rate a large matrix product reached (1366
-// TFLOP/s bf16, 154 fp32, on 256 CUs).
-template <typename T> constexpr double kCuRate = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / (kXCDs * kCUsPerXCD);
+// Time of `contractions` tile contractions of one 16-row block, in us at 85% of the
+// rate that a large matrix product reached on one CU (1366 TFLOP/s bf16, 154 fp32,
+// on 256 CUs).
+template <typename T> double block_us(int contractions, int64_t d) {
+  constexpr double kRate = (sizeof(T) == 2 ? 1366e6 : 154e6) * 0.85 / 256;  // FLOP per us
+  return 2.0 * contractions * 16 * kBS * (double)d / kRate;
+}
 
 // ---------------------------------------------------------------------------
 // Small grids: blocks of 16 nw stationary rows (nw = 4, 2, 1), with as many wave
@@ -197,28 +194,6 @@ template <typename T, int D> constexpr SetShape set_shape(int nw, int tensors, i
   while (2 * ks * nw <= max_waves && 2 * ks * (ring + extra) <= 160 * 1024) ks *= 2;
   return {nw, ks, std::max(occ, ks * nw / 4)};
 }
-// One form of a kernel as pick_form() prices it: 16-row blocks per workgroup,
-// wave sets, workgroups that fit one CU (0: not built), workgroups that split a
-// block (column kernels) and what adding their parts takes, and what a block
-// weighs in a step (more where it reads more LDS bytes per MFMA).
-struct Form {
-  int blocks = 0, sets = 1, resident = 0, parts = 1;
-  double extra_us = 0, weight = 1;
-};
-// What the forms of one launch are chosen for: heads of N rows, each block
-// streaming `tiles` tiles (all of them or, causal, up to the diagonal), with
-// `contractions` tile contractions each.
-// One step (a streamed tile of every wave set on a CU) with n 16-row blocks takes
-// base + per_block weight n times the MFMA time of one block.
-struct FormQuery {
-  int64_t heads, N, tiles, d;
-  bool causal;
-  int contractions;
-  double rate;  // FLOP per us of one CU
-  double base, per_block;
-};
-// Index of the form with the least estimated time.
-int pick_form(const FormQuery& q, std::initializer_list<Form> forms);
 
 // ---------------------------------------------------------------------------
 // Column kernels (the first backward's dK, dV and Pass 2's Kt, Vt): how one
@@ -261,9 +236,6 @@ struct ColumnPlan {
   bool wide = false;   // Pass 2 in the kP2W shape
   bool pairs = false;  // Pass 2 in wave pairs (kP2P)
 };
-
-// Compute units of the current device (0 if it cannot be read).
-int device_cus();
 
 // Automatic part count for a column grid of `workgroups` with at least
 // kLongBlock streamed iterations per block.
@@ -426,6 +398,7 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
     return BOB_EINVAL;
   using S0 = ColumnShape<T, D, kPass2, false>;
   using SF = ColumnShape<T, D, kPass2, true>;
+  const int cus = device_cus();
   auto fill = [&](auto shape, auto f) {
     constexpr Shape s = decltype(shape)::kS;
     constexpr bool two_fit = decltype(shape)::kTwoFit;
@@ -438,7 +411,7 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
     else if (iters >= kLongBlock)
       c.parts = resolve_parts(c.g.total, p.causal != 0, kPass2);
     int narrow = 0;
-    if (c.parts == 1 && device_cus() > 0) {
+    if (c.parts == 1 && cus > 0) {
       constexpr bool kSection = decltype(f)::value;
       Form whole{s.mr * s.nw, 1, 1}, n4, n2, n1, split[kMaxParts + 1];
       if (two)
@@ -450,12 +423,12 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
       // N10099 d128: unsplit 2254 us, four parts 2482; B1 H16 Hkv8 N6000: two parts 1084)
       if constexpr (!kSection && kPass2 && Cfg<T, D>::kP2W.mr > 0)
         if (constexpr Shape w = Cfg<T, D>::kP2W; !two && o.wave_sets == 0 && !p.causal && o.flush_tiles <= 0 &&
-            grid_for(p, 16 * w.mr * w.nw, true).total >= device_cus())
+            grid_for(p, 16 * w.mr * w.nw, true).total >= cus)
           whole = {w.mr * w.nw, 1, 1, 1, 0.0, 0.92};
       // narrow blocks: on grids with no more whole blocks than CUs, where wave
       // sets may be chosen and the whole block does not run in wave pairs
       if constexpr (!kSection && !(kPass2 && Cfg<T, D>::kP2P.mr > 0))
-        if (o.wave_sets != 1 && o.flush_tiles <= 0 && c.g.total <= device_cus()) {
+        if (o.wave_sets != 1 && o.flush_tiles <= 0 && c.g.total <= cus) {
           n4 = narrow_form<T, D, kPass2, 4>();
           n2 = narrow_form<T, D, kPass2, 2>();
           n1 = narrow_form<T, D, kPass2, 1>();
@@ -467,7 +440,8 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
           split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), n,
                       4.0 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};
       const int form = pick_form(
-          {p.B * p.Hkv, p.N, iters, p.d, p.causal != 0, kPass2 ? 8 : 4, kCuRate<T>, kPass2 ? 6.0 : 8.0, kPass2 ? 1.2 : 0.8},
+          {cus, p.B * p.Hkv, p.N, iters, p.causal != 0, block_us<T>(kPass2 ? 8 : 4, p.d), kPass2 ? 6.0 : 8.0,
+           kPass2 ? 1.2 : 0.8},
           {whole, n4, n2, n1, split[2], split[3], split[4], split[5], split[6], split[7], split[8]});
       if (form >= 4) c.parts = form - 2;
       else if (form >= 1) narrow = 8 >> form;
@@ -500,7 +474,6 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
   // does the same arithmetic), which a forced wave_sets = 1 still runs.
   if constexpr (kPass2 && Cfg<T, D>::kP2W.mr > 0) {
     constexpr Shape w = Cfg<T, D>::kP2W;
-    const int cus = device_cus();
     if (o.wave_sets == 0 && !p.causal && c.parts == 1 && c.sets == 1 && c.flush_tiles <= 0 && cus > 0) {
       const Grid gw = grid_for(p, 16 * w.mr * w.nw, true);
       if (gw.total >= cus) {
@@ -525,7 +498,7 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
 
 // The query of a row kernel's launch.
 template <typename T> FormQuery row_query(const Problem& p, int contractions) {
-  return {p.B * p.H, p.N, (p.N + kBS - 1) / kBS, p.d, p.causal != 0, contractions, kCuRate<T>, 4.5, 0.45};
+  return {device_cus(), p.B * p.H, p.N, (p.N + kBS - 1) / kBS, p.causal != 0, block_us<T>(contractions, p.d), 4.5, 0.45};
 }
 
 template <typename T, int D, int NW> struct FwdSmall {

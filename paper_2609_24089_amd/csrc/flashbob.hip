@@ -10,12 +10,16 @@ namespace fb {
 template int32_t launch_parts_reduce<bf16>(const Problem&, int, const float*, float, void*, void*, hipStream_t);
 template int32_t launch_parts_reduce<float>(const Problem&, int, const float*, float, void*, void*, hipStream_t);
 
-// Compute units of the current device, read from the runtime on every call
-// (the library keeps no state of its own).
+// Compute units of the current device, a constant of the device that is read from
+// the runtime once (every launch asks for it).
+constexpr int kMaxDevices = 64;
 int device_cus() {
+  static std::atomic<int> known[kMaxDevices];
   int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  if (dev < kMaxDevices && (n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
   if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 0;
+  if (dev < kMaxDevices) known[dev].store(n, std::memory_order_relaxed);
   return n;
 }
 
@@ -49,64 +53,6 @@ int resolve_parts(int workgroups, bool causal, bool pass2) {
   const int64_t target = (int64_t)(fill_only ? 2 : 8) * cus;
   const int64_t parts = (target + workgroups - 1) / workgroups;
   return parts < 2 ? 1 : (int)std::min<int64_t>(parts, kMaxParts);
-}
-
-// Estimated time of a kernel's forms.  Equal (dense) blocks cost the rounds of
-// the fullest CU, causal ones the larger of the mean load and the heaviest
-// block's steps; a step has at least the four 16-row blocks that occupy every
-// SIMD, and kRound is a round's prologue, epilogue and merge of the sets.  The
-// constants (here, and the queries' base and per_block) were fitted to 37 shapes
-// (N = 256 to 32768, 1 to 48 heads, both types, every head dim) timed in every form:
-// the row kernels' choice is on average 1.2% slower than the best form (at most
-// 23%), the column kernels' 2% (18%).
-// Measured, whole blocks -> chosen form (us), row kernels: bf16 B1 H1 N8192 d64
-// causal forward 136 -> 34, Pass 1 206 -> 100; B1 H4 N4096 d128 dense 105 -> 48, 229
-// -> 152; B2 H4 N777 d128 26 -> 13, 55 -> 33; fp32 B1 H1 N256 d64 14 -> 7, 46 -> 27.
-// Column kernels, in sets: bf16 B1 H1 N256 d64 Pass 2 15 -> 7; B1 H12 N1024 d64
-// causal 38 -> 21; split in parts: B1 H16 Hkv4 N4099 d128 causal Pass 2 606 -> 281,
-// first backward 721 -> 277; B1 H8 Hkv1 N1024 d128 causal Pass 2 258 -> 51; fp32
-// B1 H6 Hkv2 N700 d128 Pass 2 609 -> 101, first backward 347 -> 101.
-int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
-  constexpr int kCUs = kXCDs * kCUsPerXCD;
-  constexpr double kRound = 4.0;
-  const double block_us = 2.0 * q.contractions * 16 * kBS * (double)q.d / q.rate;  // one 16-row block, one tile
-  int best = 0, i = -1;
-  bool fills = false;
-  double least = 0;
-  for (const Form& f : forms) {
-    ++i;
-    if (f.resident == 0) continue;  // not built
-    const int64_t total = q.heads * ((q.N + 16 * f.blocks - 1) / (16 * f.blocks)) * f.parts;
-    // whole blocks that fill every slot of the device stay unless they are split
-    // (bf16 B1 H20 N1800 d256 causal, 580 blocks in 512 slots: forward 64 us, 72 in
-    // two sets)
-    if (i == 0) fills = f.resident > 1 && total > kCUs * f.resident;
-    if (i > 0 && ((fills && f.parts == 1) || total > INT32_MAX)) continue;
-    const int64_t shares = (int64_t)f.sets * f.parts;
-    const double share = (double)((q.tiles + shares - 1) / shares);
-    auto step = [&](int64_t workgroups) {
-      return block_us * (q.base + q.per_block * f.weight * std::max<int64_t>(4, workgroups * f.blocks * f.sets));
-    };
-    const int64_t k = (total + kCUs - 1) / kCUs;  // workgroups of the fullest CU
-    double t;
-    if (q.causal) {
-      const int64_t n = std::min<int64_t>(k, f.resident);
-      const double mean = 0.5 * (share + 1) * total / (double)kCUs / n * step(n);
-      t = std::max(mean, share * step(1));
-    } else {
-      t = share * ((double)(k / f.resident) * step(f.resident) + (k % f.resident != 0 ? step(k % f.resident) : 0));
-    }
-    t += kRound * (double)((k + f.resident - 1) / f.resident);
-    // equal blocks are split only for a clear gain: an estimated gain of a few percent
-    // was a loss (fp32 B1 H12 Hkv6 N5050 d64 Pass 2: 2481 us split, 2434 unsplit)
-    if (!q.causal && f.parts > 1) t *= 1.08;
-    t += f.extra_us;
-    if (i == 0 || t < least) {
-      best = i;
-      least = t;
-    }
-  }
-  return best;
 }
 
 static ColumnOpts opts_of(const bob_column_opts* o) {
@@ -197,7 +143,6 @@ static int32_t run_pass2(const Problem& p, const ColumnOpts& o, const void* Q, c
 // current device, read once per device and kept in scratch_dev.
 constexpr int64_t kScratchBytes = int64_t(64) << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
-constexpr int kMaxDevices = 64;
 static std::atomic<void*> scratch_dev[kMaxDevices];
 
 // Device address of `scratch` on the current device, or nullptr if it

@@ -1,0 +1,79 @@
+"""The choice of a launch's form (csrc/fb_forms.h), built with the host compiler:
+it follows the compute units that the device has."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2609_24089_amd as fb
+
+WRAPPER = r"""
+#include "fb_forms.h"
+#include <vector>
+extern "C" int balanced(int64_t total, int fit, int cus) { return fb::balanced_order(total, fit, cus); }
+extern "C" int pick(const fb::FormQuery* q, int n, const fb::Form* f) {
+  switch (n) {
+    case 2: return fb::pick_form(*q, {f[0], f[1]});
+    case 3: return fb::pick_form(*q, {f[0], f[1], f[2]});
+    case 5: return fb::pick_form(*q, {f[0], f[1], f[2], f[3], f[4]});
+  }
+  return -1;
+}
+"""
+
+
+class Form(ctypes.Structure):
+    _fields_ = [("blocks", ctypes.c_int), ("sets", ctypes.c_int), ("resident", ctypes.c_int), ("parts", ctypes.c_int),
+                ("extra_us", ctypes.c_double), ("weight", ctypes.c_double)]
+
+    def __init__(self, blocks, sets, resident, parts=1, extra_us=0.0, weight=1.0):
+        super().__init__(blocks, sets, resident, parts, extra_us, weight)
+
+
+class Query(ctypes.Structure):
+    _fields_ = [("cus", ctypes.c_int), ("heads", ctypes.c_int64), ("N", ctypes.c_int64), ("tiles", ctypes.c_int64),
+                ("causal", ctypes.c_bool), ("block_us", ctypes.c_double), ("base", ctypes.c_double),
+                ("per_block", ctypes.c_double)]
+
+
+@pytest.fixture(scope="module")
+def forms(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("forms")
+    src, out = str(tmp / "forms.cpp"), str(tmp / "forms.so")
+    with open(src, "w") as f:
+        f.write(WRAPPER)
+    csrc = os.path.join(os.path.dirname(fb.__file__), "csrc")
+    subprocess.run([os.environ.get("CXX") or shutil.which("g++"), "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC",
+                    "-shared", "-I", csrc, "-o", out, src], check=True)
+    lib = ctypes.CDLL(out)
+    lib.balanced.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    lib.pick.argtypes = [ctypes.POINTER(Query), ctypes.c_int, ctypes.c_void_p]
+    return lib
+
+
+def pick(lib, cus, heads, N, forms, causal=False):
+    q = Query(cus, heads, N, (N + 31) // 32, causal, 0.1, 4.5, 0.45)
+    return lib.pick(ctypes.byref(q), len(forms), (Form * len(forms))(*forms))
+
+
+def test_the_choice_follows_the_device(forms):
+    """32 whole blocks of 128 rows: narrow blocks in sets on 256 compute units, which
+    the whole blocks leave idle, and whole blocks on 32 (one each) or where the
+    device is unknown."""
+    f = [Form(8, 1, 2), Form(1, 8, 1)]
+    assert pick(forms, 256, 8, 512, f) == 1
+    assert pick(forms, 32, 8, 512, f) == 0
+    assert pick(forms, 0, 8, 512, f) == 0
+    # 600 whole blocks, more than fit 256 compute units at two each: no other form is weighed
+    assert pick(forms, 256, 150, 512, f) == 0
+
+
+def test_the_balanced_order_is_for_the_whole_device(forms):
+    assert forms.balanced(1024, 2, 256) == 2
+    assert forms.balanced(256, 2, 256) == 0            # one round
+    assert forms.balanced(6 * 256 * 2, 2, 256) == 2    # six rounds
+    assert forms.balanced(6 * 256 * 2 + 1, 2, 256) == 0
+    for cus in (0, 32, 64, 128, 304):                  # a part of a device, or another one
+        assert forms.balanced(1024, 2, cus) == 0
