@@ -2,6 +2,7 @@
 // on sizes alone (no HIP), so that a host compiler can build and test it.
 #pragma once
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <initializer_list>
 
@@ -11,6 +12,14 @@ namespace fb {
 // which the dispatcher deals the workgroups in turn, of 32 compute units.
 constexpr int kXCDs = 8;
 constexpr int kCUsPerXCD = 32;
+
+// A positive constant of the device that read() tells (0: it cannot be read now),
+// kept in `known` once it has been read.  Threads that read it at once keep the same.
+template <class F> int read_once(std::atomic<int>& known, F&& read) {
+  int n = known.load(std::memory_order_relaxed);
+  if (n <= 0 && (n = read()) > 0) known.store(n, std::memory_order_relaxed);
+  return n;
+}
 
 // The `resident` argument of a causal grid's launch (`fit` workgroups of the kernel
 // fit one of the device's `cus` compute units) if it is to run in the balanced order

@@ -153,12 +153,12 @@ int device_cus();
 // Workgroups of kKernel that fit one CU (1 if the runtime cannot tell), read
 // once per kernel: a property of its code object.
 template <auto kKernel> int resident_blocks(int threads) {
-  static const int resident = [&] {
+  static std::atomic<int> known;
+  return std::max(1, read_once(known, [&] {
     int n = 0;
     const hipError_t rc = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)kKernel, threads, 0);
-    return rc == hipSuccess && n > 0 ? n : 1;
-  }();
-  return resident;
+    return rc == hipSuccess ? n : 0;
+  }));
 }
 
 // The `resident` argument of a launch of kKernel (balanced_order()).

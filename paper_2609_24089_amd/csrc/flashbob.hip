@@ -15,12 +15,12 @@ template int32_t launch_parts_reduce<float>(const Problem&, int, const float*, f
 constexpr int kMaxDevices = 64;
 int device_cus() {
   static std::atomic<int> known[kMaxDevices];
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
-  if (dev < kMaxDevices && (n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 0;
-  if (dev < kMaxDevices) known[dev].store(n, std::memory_order_relaxed);
-  return n;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+  return read_once(known[dev], [&] {
+    int n = 0;
+    return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+  });
 }
 
 // Dispatch on (dtype, d) to a templated function.

@@ -13,6 +13,12 @@ WRAPPER = r"""
 #include "fb_forms.h"
 #include <vector>
 extern "C" int balanced(int64_t total, int fit, int cus) { return fb::balanced_order(total, fit, cus); }
+extern "C" int kept(const int* answers, int n, int* got) {  // the answers that n reads give in turn
+  std::atomic<int> known{0};
+  int reads = 0;
+  for (int i = 0; i < n; ++i) got[i] = fb::read_once(known, [&] { return answers[reads++]; });
+  return reads;
+}
 extern "C" int pick(const fb::FormQuery* q, int n, const fb::Form* f) {
   switch (n) {
     case 2: return fb::pick_form(*q, {f[0], f[1]});
@@ -77,3 +83,9 @@ def test_the_balanced_order_is_for_the_whole_device(forms):
     assert forms.balanced(6 * 256 * 2 + 1, 2, 256) == 0
     for cus in (0, 32, 64, 128, 304):                  # a part of a device, or another one
         assert forms.balanced(1024, 2, cus) == 0
+
+
+def test_a_constant_that_could_not_be_read_is_read_again(forms):
+    answers, got = (ctypes.c_int * 5)(0, -1, 3, 7, 7), (ctypes.c_int * 5)()
+    assert forms.kept(answers, 5, got) == 3
+    assert [max(0, g) for g in got] == [0, 0, 3, 3, 3]
