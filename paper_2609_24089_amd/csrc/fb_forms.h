@@ -36,11 +36,11 @@ inline int balanced_order(int64_t total, int fit, int cus) {
 }
 
 // One form of a kernel as pick_form() prices it: 16-row blocks per workgroup,
-// wave sets, workgroups that fit one CU (0: not built), workgroups that split a
-// block (column kernels) and what adding their parts takes, and what a block
-// weighs in a step (more where it reads more LDS bytes per MFMA).
+// wave sets, workgroups that fit one CU (0: not built), threads per workgroup,
+// workgroups that split a block (column kernels) and what adding their parts takes,
+// and what a block weighs in a step (more where it reads more LDS bytes per MFMA).
 struct Form {
-  int blocks = 0, sets = 1, resident = 0, parts = 1;
+  int blocks = 0, sets = 1, resident = 0, threads = 256, parts = 1;
   double extra_us = 0, weight = 1;
 };
 // What the forms of one launch are chosen for: heads of N rows, each block
@@ -85,7 +85,10 @@ inline int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
     // (bf16 B1 H20 N1800 d256 causal, 580 blocks in 512 slots: forward 64 us, 72 in
     // two sets)
     if (i == 0) fills = f.resident > 1 && total > q.cus * f.resident;
-    if (i > 0 && ((fills && f.parts == 1) || total > INT32_MAX)) continue;
+    // a launch takes fewer than 2^32 threads: 2^22 blocks of 1024, which 4 GB of bf16
+    // d = 32 rows in 16-row blocks reach
+    const bool launches = total <= INT32_MAX && total * f.threads <= (int64_t)UINT32_MAX;
+    if (i > 0 && ((fills && f.parts == 1) || !launches)) continue;
     const int64_t shares = (int64_t)f.sets * f.parts;
     const double share = (double)((q.tiles + shares - 1) / shares);
     auto step = [&](int64_t workgroups) {

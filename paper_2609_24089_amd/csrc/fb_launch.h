@@ -119,9 +119,10 @@ inline int32_t check_problem(const Problem& p, bool* empty) {
     return BOB_OK;
   }
   if (p.N > kMaxN) return BOB_EINVAL;
-  // 32-bit grid and loop counts: heads x row blocks (the smallest block is 64
-  // rows) sizes the grid, and a column kernel streams up to H/Hkv heads of
-  // ceil(N/32) tiles in one loop, so heads x 32-row tiles must fit an int
+  // 32-bit grid and loop counts: heads x row blocks sizes the grid (the whole block
+  // shapes have 64 rows or more; pick_form() takes no narrower one whose grid is too
+  // large), and a column kernel streams up to H/Hkv heads of ceil(N/32) tiles in one
+  // loop, so heads x 32-row tiles must fit an int
   const int64_t heads = p.B * p.H;
   if (p.B > INT32_MAX || p.H > INT32_MAX || heads > INT32_MAX) return BOB_EINVAL;
   if (heads * ((p.N + 31) / 32) > INT32_MAX) return BOB_EINVAL;
@@ -337,7 +338,7 @@ template <typename T, int D, int NW> struct Pass2Small {
 template <typename T, int D, int NW> Form ColsSmall<T, D, NW>::form() {
   // 16 rows per wave with K in registers read an LDS operand per bf16 MFMA, the
   // whole shape about 0.6
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 1, 0.0, sizeof(T) == 2 ? 1.6 : 1.0};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks, 1, 0.0, sizeof(T) == 2 ? 1.6 : 1.0};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -355,7 +356,7 @@ int32_t ColsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void*
   return BOB_EUNSUPPORTED;
 }
 template <typename T, int D, int NW> Form Pass2Small<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -413,7 +414,7 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
     int narrow = 0;
     if (c.parts == 1 && cus > 0) {
       constexpr bool kSection = decltype(f)::value;
-      Form whole{s.mr * s.nw, 1, 1}, n4, n2, n1, split[kMaxParts + 1];
+      Form whole{s.mr * s.nw, 1, 1, 64 * s.nw}, n4, n2, n1, split[kMaxParts + 1];
       if (two)
         whole.sets = 2;
       else if constexpr (!kSection)
@@ -424,7 +425,7 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
       if constexpr (!kSection && kPass2 && Cfg<T, D>::kP2W.mr > 0)
         if (constexpr Shape w = Cfg<T, D>::kP2W; !two && o.wave_sets == 0 && !p.causal && o.flush_tiles <= 0 &&
             grid_for(p, 16 * w.mr * w.nw, true).total >= cus)
-          whole = {w.mr * w.nw, 1, 1, 1, 0.0, 0.92};
+          whole = {w.mr * w.nw, 1, 1, 64 * w.nw, 1, 0.0, 0.92};
       // narrow blocks: on grids with no more whole blocks than CUs, where wave
       // sets may be chosen and the whole block does not run in wave pairs
       if constexpr (!kSection && !(kPass2 && Cfg<T, D>::kP2P.mr > 0))
@@ -437,7 +438,7 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
       // and a launch; not where wave sets are asked for, which a split has none of
       if (o.parts == 0 && o.wave_sets == 0 && iters < kLongBlock && iters >= o.min_iters)
         for (int n = 2; n <= kMaxParts; ++n)
-          split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), n,
+          split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), 64 * s.nw, n,
                       4.0 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};
       const int form = pick_form(
           {cus, p.B * p.Hkv, p.N, iters, p.causal != 0, block_us<T>(kPass2 ? 8 : 4, p.d), kPass2 ? 6.0 : 8.0,
@@ -509,7 +510,7 @@ template <typename T, int D, int NW> struct FwdSmall {
                         hipStream_t s);
 };
 template <typename T, int D, int NW> Form FwdSmall<T, D, NW>::form() {
-  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
 }
 template <typename T, int D, int NW>
 int32_t FwdSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
@@ -537,7 +538,7 @@ template <typename T, int D> struct FwdWide {
                         hipStream_t s);
 };
 template <typename T, int D> Form FwdWide<T, D>::form() {
-  if constexpr (kBuilt) return {kS.mr * kS.nw, 2, resident_blocks<kernel()>(128 * kS.nw)};
+  if constexpr (kBuilt) return {kS.mr * kS.nw, 2, resident_blocks<kernel()>(128 * kS.nw), 128 * kS.nw};
   else return {};
 }
 template <typename T, int D>
@@ -564,7 +565,7 @@ template <typename T, int D> struct RowsWide {
                         const float* L, void* dQ, float* Dv, hipStream_t s);
 };
 template <typename T, int D> Form RowsWide<T, D>::form() {
-  if constexpr (kBuilt) return {kS.mr * kS.nw, 2, resident_blocks<kernel()>(128 * kS.nw)};
+  if constexpr (kBuilt) return {kS.mr * kS.nw, 2, resident_blocks<kernel()>(128 * kS.nw), 128 * kS.nw};
   else return {};
 }
 template <typename T, int D>
@@ -592,7 +593,7 @@ template <typename T, int D, int NW> struct RowsSmall {
                         const float* L, void* dQ, float* Dv, hipStream_t s);
 };
 template <typename T, int D, int NW> Form RowsSmall<T, D, NW>::form() {
-  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
 }
 template <typename T, int D, int NW>
 int32_t RowsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
@@ -620,7 +621,7 @@ template <typename T, int D, int NW> struct Pass1Small {
                         const void* dQ, void* Qt, void* dOt, float* alpha, float* E, hipStream_t s);
 };
 template <typename T, int D, int NW> Form Pass1Small<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks)};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -663,7 +664,7 @@ int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V
   using F2 = FwdSmall<T, D, 2>;
   using F1 = FwdSmall<T, D, 1>;
   switch (pick_form(row_query<T>(p, 2),
-                   {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form(),
+                   {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw), 64 * c.nw}, F4::form(), F2::form(), F1::form(),
                     FwdWide<T, D>::form()})) {
     case 1: return F4::launch(p, Q, K, V, O, L, s);
     case 2: return F2::launch(p, Q, K, V, O, L, s);
@@ -747,7 +748,7 @@ int32_t launch_bwd_rows(const Problem& p, const void* Q, const void* K, const vo
   using F2 = RowsSmall<T, D, 2>;
   using F1 = RowsSmall<T, D, 1>;
   switch (pick_form(row_query<T>(p, 3),
-                   {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw)}, F4::form(), F2::form(), F1::form(),
+                   {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw), 64 * cr.nw}, F4::form(), F2::form(), F1::form(),
                     RowsWide<T, D>::form()})) {
     case 1: return F4::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
     case 2: return F2::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
@@ -790,7 +791,7 @@ int32_t launch_pass1(const Problem& p, const void* Q, const void* K, const void*
     using F2 = Pass1Small<T, D, 2>;
     using F1 = Pass1Small<T, D, 1>;
     switch (pick_form(row_query<T>(p, 10),
-                     {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw)}, F4::form(), F2::form(), F1::form()})) {
+                     {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw), 64 * c.nw}, F4::form(), F2::form(), F1::form()})) {
       case 1: return F4::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
       case 2: return F2::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
       case 3: return F1::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);

@@ -16,8 +16,9 @@ constexpr int kMaxDevices = 64;
 int device_cus() {
   static std::atomic<int> known[kMaxDevices];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-  return read_once(known[dev], [&] {
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  std::atomic<int> beyond{0};
+  return read_once(dev < kMaxDevices ? known[dev] : beyond, [&] {
     int n = 0;
     return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
   });

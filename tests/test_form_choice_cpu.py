@@ -31,11 +31,11 @@ extern "C" int pick(const fb::FormQuery* q, int n, const fb::Form* f) {
 
 
 class Form(ctypes.Structure):
-    _fields_ = [("blocks", ctypes.c_int), ("sets", ctypes.c_int), ("resident", ctypes.c_int), ("parts", ctypes.c_int),
-                ("extra_us", ctypes.c_double), ("weight", ctypes.c_double)]
+    _fields_ = [("blocks", ctypes.c_int), ("sets", ctypes.c_int), ("resident", ctypes.c_int), ("threads", ctypes.c_int),
+                ("parts", ctypes.c_int), ("extra_us", ctypes.c_double), ("weight", ctypes.c_double)]
 
-    def __init__(self, blocks, sets, resident, parts=1, extra_us=0.0, weight=1.0):
-        super().__init__(blocks, sets, resident, parts, extra_us, weight)
+    def __init__(self, blocks, sets, resident, threads=256, parts=1, extra_us=0.0, weight=1.0):
+        super().__init__(blocks, sets, resident, threads, parts, extra_us, weight)
 
 
 class Query(ctypes.Structure):
@@ -89,3 +89,16 @@ def test_a_constant_that_could_not_be_read_is_read_again(forms):
     answers, got = (ctypes.c_int * 5)(0, -1, 3, 7, 7), (ctypes.c_int * 5)()
     assert forms.kept(answers, 5, got) == 3
     assert [max(0, g) for g in got] == [0, 0, 3, 3, 3]
+
+
+@pytest.mark.parametrize("threads", [256, 512, 1024])
+def test_no_form_that_a_launch_cannot_take(forms, threads):
+    """Problems of one 16-row block a head: the narrow form wins until its grid has
+    2^32 threads, and from there on the whole form runs."""
+    most = (2 ** 32 - 1) // threads
+    f = [Form(4, 1, 1), Form(1, threads // 64, 4, threads=threads)]
+    assert pick(forms, 256, most, 16, f) == 1
+    assert pick(forms, 256, most + 1, 16, f) == 0
+    f = [Form(4, 1, 1), Form(1, 1, 16, threads=1, weight=0.01)]   # 2^31 blocks
+    assert pick(forms, 256, 2 ** 31 - 1, 16, f) == 1
+    assert pick(forms, 256, 2 ** 31, 16, f) == 0
