@@ -131,6 +131,7 @@ typedef struct {
 } bob_column_opts;
 
 enum { BOB_COLUMNS_BWD = 0, BOB_COLUMNS_PASS2 = 1 };
+enum { BOB_ROWS_FWD = 0, BOB_ROWS_BWD = 1, BOB_ROWS_PASS1 = 2 };
 
 /* Forward attention (eq. 1) with its log-normalizer (Sec. 2).
  * In:  Q, K, V  [B,H,N,d].
@@ -253,6 +254,16 @@ int64_t bob_bwd_workspace_bytes(int32_t dtype, int64_t B, int64_t H, int64_t Hkv
 int32_t bob_column_layout(int32_t kernel, int32_t dtype, int64_t B, int64_t H, int64_t Hkv, int64_t N, int64_t d,
                           int32_t causal, const bob_column_opts* opts, bob_column_opts* resolved,
                           int64_t* workspace_bytes);
+
+/* The layout a row kernel runs for this problem on the current device (kernel:
+ * BOB_ROWS_FWD, BOB_ROWS_BWD for the first backward's dQ and D, BOB_ROWS_PASS1
+ * for Pass 1 with dQ given): `rows` (may be NULL) receives the query rows per
+ * workgroup and `wave_sets` (may be NULL) the wave sets that share the streamed
+ * key tiles; both 0 and 1 for an empty problem.  The library chooses it by
+ * estimated time; there is nothing to request.  Returns BOB_OK, or the status
+ * the call would return for the problem (scale and pointers aside). */
+int32_t bob_row_layout(int32_t kernel, int32_t dtype, int64_t B, int64_t H, int64_t Hkv, int64_t N, int64_t d,
+                       int32_t causal, int32_t* rows, int32_t* wave_sets);
 
 /* Pass 2 for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): as

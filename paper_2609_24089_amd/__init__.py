@@ -21,6 +21,7 @@ BOB_F32 = 0
 BOB_BF16 = 1
 BOB_OK, BOB_EINVAL, BOB_EUNSUPPORTED, BOB_ELAUNCH, BOB_ESCRATCH = 0, 1, 2, 3, 4
 BOB_COLUMNS_BWD, BOB_COLUMNS_PASS2 = 0, 1
+BOB_ROWS_FWD, BOB_ROWS_BWD, BOB_ROWS_PASS1 = 0, 1, 2
 
 _lib = None
 _native = None  # csrc/torch_binding.cpp, bound to the loaded library
@@ -79,6 +80,8 @@ def load_library():
     lib.bob_column_layout.argtypes = [i32, i32, i64, i64, i64, i64, i64, i32, opts_p, opts_p,
                                       ctypes.POINTER(i64)]
     lib.bob_column_layout.restype = i32
+    lib.bob_row_layout.argtypes = [i32, i32, i64, i64, i64, i64, i64, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.bob_row_layout.restype = i32
     lib.attn_bob_pass2_cols_gqa_ws.argtypes = common_gqa + [vp] * 13 + [opts_p, vp, i64] + [vp]
     lib.attn_bob_pass2_cols_gqa_ws.restype = i32
     lib.attn_bwd_gqa_ws.argtypes = common_gqa + [vp] * 10 + [opts_p, vp, i64] + [vp]
@@ -132,6 +135,21 @@ def column_layout(kernel, dtype, B, H, Hkv, N, d, causal=False, columns=None, de
     if rc != BOB_OK:
         raise RuntimeError(status_string(rc))
     return got, nbytes.value
+
+
+def row_layout(kernel, dtype, B, H, Hkv, N, d, causal=False, device=None):
+    """bob_row_layout: (query rows per workgroup, wave sets) of the row kernel
+    `kernel` (BOB_ROWS_FWD, BOB_ROWS_BWD or BOB_ROWS_PASS1) for this problem on
+    `device` (default: the current device)."""
+    lib = load_library()
+    code = _dtype_code(torch.empty(0, dtype=dtype))
+    rows, sets = ctypes.c_int32(0), ctypes.c_int32(0)
+    with torch.cuda.device(device if device is not None else torch.cuda.current_device()):
+        rc = lib.bob_row_layout(kernel, code, B, H, Hkv, N, d, int(bool(causal)), ctypes.byref(rows),
+                                ctypes.byref(sets))
+    if rc != BOB_OK:
+        raise RuntimeError(status_string(rc))
+    return rows.value, sets.value
 
 
 def _dtype_code(t):

@@ -71,8 +71,10 @@ struct FormQuery {
 // first backward 721 -> 277; B1 H8 Hkv1 N1024 d128 causal Pass 2 258 -> 51; fp32
 // B1 H6 Hkv2 N700 d128 Pass 2 609 -> 101, first backward 347 -> 101.
 // Returns the index of the form with the least time; 0 if the device is unknown.
-inline int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
+// *chosen (may be null): that form.
+inline int pick_form(const FormQuery& q, std::initializer_list<Form> forms, Form* chosen = nullptr) {
   constexpr double kRound = 4.0;
+  if (chosen != nullptr) *chosen = *forms.begin();
   if (q.cus <= 0) return 0;
   int best = 0, i = -1;
   bool fills = false;
@@ -113,6 +115,7 @@ inline int pick_form(const FormQuery& q, std::initializer_list<Form> forms) {
       least = t;
     }
   }
+  if (chosen != nullptr) *chosen = forms.begin()[best];
   return best;
 }
 

@@ -655,20 +655,40 @@ FB_ROWS_SMALL(extern, bf16, 128)
 FB_EACH_BUT_BF16_128(FB_PASS1_SMALL, extern)
 FB_PASS1_SMALL(extern, bf16, 128)
 
+// The form that each row kernel's launch takes (its place in the list; *chosen, may
+// be null: the form).
+template <typename T, int D> int fwd_form(const Problem& p, Form* chosen = nullptr) {
+  constexpr Shape c = Cfg<T, D>::kFwd;
+  constexpr auto whole = &attn_fwd_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
+  return pick_form(row_query<T>(p, 2),
+                   {{c.mr * c.nw, 1, resident_blocks<whole>(64 * c.nw), 64 * c.nw}, FwdSmall<T, D, 4>::form(),
+                    FwdSmall<T, D, 2>::form(), FwdSmall<T, D, 1>::form(), FwdWide<T, D>::form()}, chosen);
+}
+template <typename T, int D> int bwd_rows_form(const Problem& p, Form* chosen = nullptr) {
+  constexpr Shape c = Cfg<T, D>::kRows;
+  constexpr auto whole = &attn_bwd_rows_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
+  return pick_form(row_query<T>(p, 3),
+                   {{c.mr * c.nw, 1, resident_blocks<whole>(64 * c.nw), 64 * c.nw}, RowsSmall<T, D, 4>::form(),
+                    RowsSmall<T, D, 2>::form(), RowsSmall<T, D, 1>::form(), RowsWide<T, D>::form()}, chosen);
+}
+template <typename T, int D> int pass1_form(const Problem& p, Form* chosen) {  // the dQ form
+  constexpr Shape c = Cfg<T, D>::kP1;
+  constexpr auto whole = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kWithDQ, c.ds, c.pf>;
+  return pick_form(row_query<T>(p, 10),
+                   {{c.mr * c.nw, 1, resident_blocks<whole>(64 * c.nw), 64 * c.nw}, Pass1Small<T, D, 4>::form(),
+                    Pass1Small<T, D, 2>::form(), Pass1Small<T, D, 1>::form()}, chosen);
+}
+extern template int pass1_form<bf16, 128>(const Problem&, Form*);  // built in fb_passes_d128.hip, with its kernel
+
 template <typename T, int D>
 int32_t launch_fwd(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
                    hipStream_t s) {
   constexpr Shape c = Cfg<T, D>::kFwd;
   constexpr auto kernel = &attn_fwd_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
-  using F4 = FwdSmall<T, D, 4>;
-  using F2 = FwdSmall<T, D, 2>;
-  using F1 = FwdSmall<T, D, 1>;
-  switch (pick_form(row_query<T>(p, 2),
-                   {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw), 64 * c.nw}, F4::form(), F2::form(), F1::form(),
-                    FwdWide<T, D>::form()})) {
-    case 1: return F4::launch(p, Q, K, V, O, L, s);
-    case 2: return F2::launch(p, Q, K, V, O, L, s);
-    case 3: return F1::launch(p, Q, K, V, O, L, s);
+  switch (fwd_form<T, D>(p)) {
+    case 1: return FwdSmall<T, D, 4>::launch(p, Q, K, V, O, L, s);
+    case 2: return FwdSmall<T, D, 2>::launch(p, Q, K, V, O, L, s);
+    case 3: return FwdSmall<T, D, 1>::launch(p, Q, K, V, O, L, s);
     case 4: return FwdWide<T, D>::launch(p, Q, K, V, O, L, s);
   }
   const Grid g = grid_for(p, 16 * c.mr * c.nw);
@@ -744,15 +764,10 @@ int32_t launch_bwd_rows(const Problem& p, const void* Q, const void* K, const vo
                         const float* L, void* dQ, float* Dv, hipStream_t s) {
   constexpr Shape cr = Cfg<T, D>::kRows;
   constexpr auto rows = &attn_bwd_rows_kernel<T, D, cr.mr, cr.nw, cr.occ, cr.st>;
-  using F4 = RowsSmall<T, D, 4>;
-  using F2 = RowsSmall<T, D, 2>;
-  using F1 = RowsSmall<T, D, 1>;
-  switch (pick_form(row_query<T>(p, 3),
-                   {{cr.mr * cr.nw, 1, resident_blocks<rows>(64 * cr.nw), 64 * cr.nw}, F4::form(), F2::form(), F1::form(),
-                    RowsWide<T, D>::form()})) {
-    case 1: return F4::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
-    case 2: return F2::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
-    case 3: return F1::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+  switch (bwd_rows_form<T, D>(p)) {
+    case 1: return RowsSmall<T, D, 4>::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+    case 2: return RowsSmall<T, D, 2>::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
+    case 3: return RowsSmall<T, D, 1>::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
     case 4: return RowsWide<T, D>::launch(p, Q, K, V, O, dO, L, dQ, Dv, s);
   }
   const Grid gr = grid_for(p, 16 * cr.mr * cr.nw);
@@ -787,14 +802,10 @@ int32_t launch_pass1(const Problem& p, const void* Q, const void* K, const void*
   if (dQ != nullptr) {
     constexpr Shape c = Cfg<T, D>::kP1;
     constexpr auto kernel = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kWithDQ, c.ds, c.pf>;
-    using F4 = Pass1Small<T, D, 4>;
-    using F2 = Pass1Small<T, D, 2>;
-    using F1 = Pass1Small<T, D, 1>;
-    switch (pick_form(row_query<T>(p, 10),
-                     {{c.mr * c.nw, 1, resident_blocks<kernel>(64 * c.nw), 64 * c.nw}, F4::form(), F2::form(), F1::form()})) {
-      case 1: return F4::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
-      case 2: return F2::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
-      case 3: return F1::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
+    switch (pass1_form<T, D>(p, nullptr)) {
+      case 1: return Pass1Small<T, D, 4>::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
+      case 2: return Pass1Small<T, D, 2>::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
+      case 3: return Pass1Small<T, D, 1>::launch(p, Q, K, V, O, dO, UQ, UK, UV, L, Dv, dQ, Qt, dOt, alpha, E, s);
     }
     const Grid g = grid_for(p, 16 * c.mr * c.nw);
     const int res = causal_resident<kernel>(p, g, 64 * c.nw);

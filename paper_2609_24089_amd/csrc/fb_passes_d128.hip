@@ -22,6 +22,7 @@ template int32_t launch_pass2<bf16, 128>(const Problem&, const void*, const void
                                          const float*, const float*, void*, void*, hipStream_t, const ColumnPlan&,
                                          float*);
 
+template int pass1_form<bf16, 128>(const Problem&, Form*);
 template int columns_resident<bf16, 128, true, false>(bool);
 template int columns_resident<bf16, 128, true, true>(bool);
 FB_PASS1_SMALL(, bf16, 128)

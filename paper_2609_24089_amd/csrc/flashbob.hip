@@ -79,6 +79,15 @@ int32_t plan_pass2(const Problem& p, const ColumnOpts& o, ColumnPlan* c) {
   return plan_columns<T, D, true>(p, o, c);
 }
 
+template <typename T, int D>
+int32_t row_form(const Problem& p, int32_t kernel, Form* f) {
+  if (kernel == BOB_ROWS_FWD) fwd_form<T, D>(p, f);
+  else if (kernel == BOB_ROWS_BWD) bwd_rows_form<T, D>(p, f);
+  else pass1_form<T, D>(p, f);
+  return BOB_OK;
+}
+static int32_t row_plan(const Problem& p, int32_t kernel, Form* f) { FB_DISPATCH(p, row_form, p, kernel, f); }
+
 // Plan of a column kernel (pass2: Pass 2, else the first backward's) for a
 // valid problem; an empty problem gets the trivial plan.
 static int32_t column_plan(const Problem& p, bool pass2, const ColumnOpts& o, ColumnPlan* c) {
@@ -301,6 +310,20 @@ int32_t bob_column_layout(int32_t kernel, int32_t dtype, int64_t B, int64_t H, i
     resolved->flush_tiles = c.flush_tiles > 0 ? c.flush_tiles : -1;
   }
   if (workspace_bytes != nullptr) *workspace_bytes = fb::column_workspace_bytes(p, c.parts);
+  return BOB_OK;
+}
+
+int32_t bob_row_layout(int32_t kernel, int32_t dtype, int64_t B, int64_t H, int64_t Hkv, int64_t N, int64_t d,
+                       int32_t causal, int32_t* rows, int32_t* wave_sets) {
+  if (kernel < BOB_ROWS_FWD || kernel > BOB_ROWS_PASS1) return BOB_EINVAL;
+  const Problem p{dtype, B, H, N, d, 1.0f, causal, Hkv};
+  bool empty;
+  int32_t rc = fb::check_problem(p, &empty);
+  if (rc != BOB_OK) return rc;
+  fb::Form f;
+  if (!empty && (rc = fb::row_plan(p, kernel, &f)) != BOB_OK) return rc;
+  if (rows != nullptr) *rows = 16 * f.blocks;
+  if (wave_sets != nullptr) *wave_sets = f.sets;
   return BOB_OK;
 }
 
