@@ -195,6 +195,10 @@ template <typename T, int D> constexpr SetShape set_shape(int nw, int tensors, i
   while (2 * ks * nw <= max_waves && 2 * ks * (ring + extra) <= 160 * 1024) ks *= 2;
   return {nw, ks, std::max(occ, ks * nw / 4)};
 }
+// Whether blocks of nw waves are worth building beside those of twice as many, the
+// next wider form: not where those have the same sets and need no more than a CU's four
+// SIMDs, so that a step takes them as long and they hold twice the rows.
+constexpr bool worth_building(SetShape s, SetShape twice) { return s.ks != twice.ks || 2 * s.nw * s.ks > 4; }
 
 // ---------------------------------------------------------------------------
 // Column kernels (the first backward's dK, dV and Pass 2's Kt, Vt): how one
@@ -307,9 +311,11 @@ extern template int columns_resident<bf16, 128, true, true>(bool);
 template <typename T, int D, int NW> struct ColsSmall {
   static constexpr int kExtra = 4 * 2 * kBS * (int)sizeof(float);  // raw and transformed L, D
   // K, V and two accumulators of 16 rows fit four waves per SIMD up to 128-byte rows
-  static constexpr SetShape kS =
-      set_shape<T, D>(NW, 2, kExtra, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kCols.occ);
-  static constexpr bool kBuilt = kS.ks > 1;
+  static constexpr SetShape shape(int nw) {
+    return set_shape<T, D>(nw, 2, kExtra, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kCols.occ);
+  }
+  static constexpr SetShape kS = shape(NW);
+  static constexpr bool kBuilt = kS.ks > 1 && worth_building(kS, shape(2 * NW));
   static __host__ constexpr auto kernel() {
     if constexpr (kBuilt)
       return &attn_bwd_cols_kernel<T, D, 1, NW, kS.occ, 2, true, kS.ks, false, false, false>;
@@ -320,12 +326,14 @@ template <typename T, int D, int NW> struct ColsSmall {
 };
 template <typename T, int D, int NW> struct Pass2Small {
   static constexpr int kExtra = 4 * 4 * kBS * (int)sizeof(float);  // raw and transformed L, D, alpha, E
-  static constexpr SetShape kS = set_shape<T, D>(NW, 3, kExtra, 8, Cfg<T, D>::kP2.occ);
+  static constexpr SetShape shape(int nw) { return set_shape<T, D>(nw, 3, kExtra, 8, Cfg<T, D>::kP2.occ); }
+  static constexpr SetShape kS = shape(NW);
   // three tensors of two 1 KB blocks (bf16 d = 32) do not deal out over four waves;
   // where four blocks in two sets are the whole shape's two sets, those run
   static constexpr bool kSameAsWhole = Cfg<T, D>::kP2.mr == 1 && Cfg<T, D>::kP2.nw == NW && kS.ks == 2 &&
                                        ColumnShape<T, D, true, false>::kTwoFit;
-  static constexpr bool kBuilt = kS.ks > 1 && !kSameAsWhole && !(sizeof(T) == 2 && D == 32 && NW == 4);
+  static constexpr bool kBuilt = kS.ks > 1 && !kSameAsWhole && !(sizeof(T) == 2 && D == 32 && NW == 4) &&
+                                 worth_building(kS, shape(2 * NW));
   static __host__ constexpr auto kernel() {
     if constexpr (kBuilt)
       return &bob_pass2_kernel<T, D, 1, NW, kS.occ, 2, true, kS.ks, Cfg<T, D>::kP2.pf != 0, false, false>;
@@ -503,24 +511,32 @@ template <typename T> FormQuery row_query(const Problem& p, int contractions) {
 }
 
 template <typename T, int D, int NW> struct FwdSmall {
-  static constexpr SetShape kS = set_shape<T, D>(NW, 2, 128 * NW, 16, Cfg<T, D>::kFwd.occ);
-  static __host__ constexpr auto kernel() { return &attn_fwd_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>; }
+  static constexpr SetShape shape(int nw) { return set_shape<T, D>(nw, 2, 128 * nw, 16, Cfg<T, D>::kFwd.occ); }
+  static constexpr SetShape kS = shape(NW);
+  static constexpr bool kBuilt = worth_building(kS, shape(2 * NW));
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt) return &attn_fwd_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
+  }
   static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
                         hipStream_t s);
 };
 template <typename T, int D, int NW> Form FwdSmall<T, D, NW>::form() {
-  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  else return {};
 }
 template <typename T, int D, int NW>
 int32_t FwdSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, void* O, float* L,
                                    hipStream_t s) {
-  const Grid g = grid_for(p, 16 * NW);
-  const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
-                     (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
-  return finish_launch();
+  if constexpr (kBuilt) {
+    const Grid g = grid_for(p, 16 * NW);
+    const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (T*)O, L, (int)p.N, g.nRB, g.total, p.scale, p.causal, res, group(p));
+    return finish_launch();
+  }
+  return BOB_EUNSUPPORTED;
 }
 
 // The whole block shape (32 rows per wave) in two wave sets, for grids that leave
@@ -556,7 +572,9 @@ int32_t FwdWide<T, D>::launch(const Problem& p, const void* Q, const void* K, co
 }
 template <typename T, int D> struct RowsWide {
   static constexpr Shape kS = Cfg<T, D>::kRows;
-  static constexpr bool kBuilt = kS.mr == 2;
+  // at d = 128 one workgroup of 16 block-sets fits a CU, as two of RowsSmall<4>'s do
+  // in the same step and finer grain
+  static constexpr bool kBuilt = kS.mr == 2 && D < 128;
   static __host__ constexpr auto kernel() {
     if constexpr (kBuilt) return &attn_bwd_rows_kernel<T, D, kS.mr, kS.nw, kS.occ, kS.st, 2>;
   }
@@ -585,33 +603,43 @@ int32_t RowsWide<T, D>::launch(const Problem& p, const void* Q, const void* K, c
 
 template <typename T, int D, int NW> struct RowsSmall {
   // two operands and an accumulator of 16 rows fit four waves per SIMD up to 128-byte rows
-  static constexpr SetShape kS =
-      set_shape<T, D>(NW, 2, 128 * NW, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kRows.occ);
-  static __host__ constexpr auto kernel() { return &attn_bwd_rows_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>; }
+  static constexpr SetShape shape(int nw) {
+    return set_shape<T, D>(nw, 2, 128 * nw, D * (int)sizeof(T) <= 128 ? 16 : 8, Cfg<T, D>::kRows.occ);
+  }
+  static constexpr SetShape kS = shape(NW);
+  static constexpr bool kBuilt = worth_building(kS, shape(2 * NW));
+  static __host__ constexpr auto kernel() {
+    if constexpr (kBuilt) return &attn_bwd_rows_kernel<T, D, 1, NW, kS.occ, 2, kS.ks>;
+  }
   static Form form();
   static int32_t launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                         const float* L, void* dQ, float* Dv, hipStream_t s);
 };
 template <typename T, int D, int NW> Form RowsSmall<T, D, NW>::form() {
-  return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  else return {};
 }
 template <typename T, int D, int NW>
 int32_t RowsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void* K, const void* V, const void* O,
                                     const void* dO, const float* L, void* dQ, float* Dv, hipStream_t s) {
-  const Grid g = grid_for(p, 16 * NW);
-  const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
-                     (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
-                     group(p));
-  return finish_launch();
+  if constexpr (kBuilt) {
+    const Grid g = grid_for(p, 16 * NW);
+    const int res = causal_resident<kernel()>(p, g, 64 * NW * kS.ks);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(kernel(), dim3(g.total), dim3(64 * NW * kS.ks), 0, s, (const T*)Q, (const T*)K, (const T*)V,
+                       (const T*)O, (const T*)dO, L, (T*)dQ, Dv, (int)p.N, g.nRB, g.total, p.scale, p.causal, res,
+                       group(p));
+    return finish_launch();
+  }
+  return BOB_EUNSUPPORTED;
 }
 
 template <typename T, int D, int NW> struct Pass1Small {
-  static constexpr SetShape kS = set_shape<T, D>(NW, 4, 128 * NW, 8, Cfg<T, D>::kP1.occ);
+  static constexpr SetShape shape(int nw) { return set_shape<T, D>(nw, 4, 128 * nw, 8, Cfg<T, D>::kP1.occ); }
+  static constexpr SetShape kS = shape(NW);
   // where no second set fits, four blocks are the whole-block shape itself and
   // not built here again
-  static constexpr bool kBuilt = NW != 4 || kS.ks > 1;
+  static constexpr bool kBuilt = (NW != 4 || kS.ks > 1) && worth_building(kS, shape(2 * NW));
   static __host__ constexpr auto kernel() {
     if constexpr (kBuilt) return &bob_pass1_kernel<T, D, 1, NW, kS.occ, 2, kWithDQ, 1, Cfg<T, D>::kP1.pf, kS.ks>;
   }

@@ -2,6 +2,7 @@
 it follows the compute units that the device has."""
 import ctypes
 import os
+import random
 import shutil
 import subprocess
 
@@ -102,3 +103,17 @@ def test_no_form_that_a_launch_cannot_take(forms, threads):
     f = [Form(4, 1, 1), Form(1, 1, 16, threads=1, weight=0.01)]   # 2^31 blocks
     assert pick(forms, 256, 2 ** 31 - 1, 16, f) == 1
     assert pick(forms, 256, 2 ** 31, 16, f) == 0
+
+
+def test_narrower_blocks_with_the_same_sets_are_never_taken(forms):
+    """Forms that are not built (worth_building() in csrc/fb_launch.h): blocks whose
+    sets are those of the next wider form, both within one step of a compute unit's
+    four SIMDs; and two-set 128-row blocks beside two 64-row ones a compute unit."""
+    rng = random.Random(7)
+    for _ in range(3000):
+        heads, N = rng.randint(1, 400), int(2 ** rng.uniform(0, 16))
+        causal, whole = rng.random() < 0.5, Form(4, 1, rng.choice((1, 2)))
+        assert pick(forms, 256, heads, N, [whole, Form(2, 2, 1), Form(1, 2, 1)], causal) != 2
+        assert pick(forms, 256, heads, N, [whole, Form(2, 1, 1), Form(1, 1, 1)], causal) == 0
+        assert pick(forms, 256, heads, N, [Form(8, 1, 2), Form(4, 2, 2), Form(2, 4, 1), Form(1, 4, 1), Form(8, 2, 1)],
+                    causal) != 4
