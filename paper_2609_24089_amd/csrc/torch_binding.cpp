@@ -2,10 +2,10 @@
 // allocated outputs on the current stream and automatic column layouts, and
 // attention() as C++ autograd functions.  Every function returns None for a call
 // that it does not take (a check fails, tensors of a functorch or dispatch-mode
-// level, tracing, forward-mode tangents); the Python code then runs the call and
-// raises what is to be raised.  Small problems are bound by the host: bob() on
-// one head of 64 rows took 107 us through ctypes and Python checks, of which the
-// five launches are about 15.
+// level, tensor subclasses, tracing, forward-mode tangents); the Python code then
+// runs the call and raises what is to be raised.  Small problems are bound by the
+// host: bob() on one head of 64 rows took 107 us through ctypes and Python checks,
+// of which the five launches are about 15.
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -178,10 +178,12 @@ P2 run_pass2(const Dims& m, const Tensor& Q, const Tensor& K, const Tensor& V, c
 // ---------------------------------------------------------------------------
 // Python arguments
 // ---------------------------------------------------------------------------
+// Tensors and Parameters alone: another subclass has a say in the type of the
+// outputs, which the Python code makes from its inputs.
 bool tensors(std::initializer_list<py::handle> hs, std::vector<Tensor>& out) {
   out.reserve(hs.size());
   for (py::handle h : hs) {
-    if (!THPVariable_Check(h.ptr())) return false;
+    if (!THPVariable_CheckExact(h.ptr())) return false;
     out.push_back(THPVariable_Unpack(h.ptr()));
   }
   return outside_modes();
@@ -222,7 +224,7 @@ py::object py_pass1(py::handle q, py::handle k, py::handle v, py::handle o, py::
   Tensor dQ;
   if (!tensors({q, k, v, o, dO, uq, uk, uv, L, D}, t)) return py::none();
   if (!dq.is_none()) {
-    if (!THPVariable_Check(dq.ptr())) return py::none();
+    if (!THPVariable_CheckExact(dq.ptr())) return py::none();
     dQ = THPVariable_Unpack(dq.ptr());
   }
   if (!check({&t[0], &t[3], &t[4], &t[5], dq.is_none() ? &t[0] : &dQ}, {&t[1], &t[2], &t[6], &t[7]}, {&t[8], &t[9]},

@@ -124,3 +124,27 @@ def test_attention_under_hooks_and_transforms(fb):
     q2.mul_(2)   # a saved input changed in place
     with pytest.raises(RuntimeError, match="inplace|in-place"):
         torch.autograd.grad(O, (k,), grad_outputs=dO)
+
+
+class Tagged(torch.Tensor):
+    """A subclass that takes part in torch's functions (by the default
+    __torch_function__, which keeps the type)."""
+
+
+def test_tensor_subclasses_keep_their_type(fb):
+    """Outputs made like an input have its class, as on the ctypes path; a Parameter
+    gives plain tensors on either."""
+    t = tensors(CASES[0], 293)
+    plain = fb.bob(*t, 0.1, causal=True)
+    sub = [x.as_subclass(Tagged) for x in t]
+    got, ref = fb.bob(*sub, 0.1, causal=True), through_ctypes(fb, *sub, 0.1, True)
+    for k in ref:
+        assert type(got[k]) is type(ref[k]) and torch.equal(got[k].as_subclass(torch.Tensor), plain[k]), k
+    assert type(got["Qt"]) is Tagged
+    assert type(fb.attention(*sub[:3], 0.1, True)) is Tagged
+    q = torch.nn.Parameter(t[0])
+    assert type(fb.attn_fwd_lse(q, *t[1:3], 0.1)[0]) is torch.Tensor
+    O = fb.attention(q, *t[1:3], 0.1, True)
+    assert type(O) is torch.Tensor and "AttentionFn" not in type(O.grad_fn).__name__   # the C++ function
+    dq, = torch.autograd.grad(O, (q,), grad_outputs=t[3])
+    assert torch.equal(dq, plain["dQ"])
