@@ -24,12 +24,12 @@ template <class F> int read_once(std::atomic<int>& known, F&& read) {
 // The `resident` argument of a causal grid's launch (`fit` workgroups of the kernel
 // fit one of the device's `cus` compute units) if it is to run in the balanced order
 // (map_block_causal), else 0 (heads one after another).  A grid of one round has a CU
-// for every block, and on grids of more than about six times the resident blocks the
-// refills balance the load by themselves while blocks of one head in flight at a time
-// share its streamed tiles in L2: measured bf16 B4 H12 N16384 d64 (24 and 48 rounds, 4
-// and 3 resident), the balanced order ran Pass 1 5% and Pass 2 3% slower and the
-// forward 2% faster; at N4096 (6 and 12 rounds) it ran Pass 1 6%, Pass 2 15% and the
-// forward 24% faster.  A part of a device (another CU count) keeps the plain order.
+// for every block, and on grids of many times the resident blocks the refills balance
+// the load by themselves while blocks of one head in flight at a time share its
+// streamed tiles in L2.  Measured on 270 kernels of causal problems, plain over
+// balanced time: up to six multiples of the resident blocks 0.99 to 1.59, median 1.15;
+// beyond eight, bf16 0.57 to 1.06, median 0.97 (fp32, whose tiles are reused longer,
+// still gains there).  A part of a device (another CU count) keeps the plain order.
 inline int balanced_order(int64_t total, int fit, int cus) {
   if (cus != kXCDs * kCUsPerXCD || total <= cus) return 0;
   return total <= (int64_t)6 * cus * fit ? fit : 0;
@@ -46,23 +46,29 @@ struct Form {
 // What the forms of one launch are chosen for: heads of N rows, each block
 // streaming `tiles` tiles (all of them or, causal, up to the diagonal).
 // One step (a streamed tile of every wave set on a CU) with n 16-row blocks takes
-// base + per_block weight n times block_us.
+// base + per_block weight n times block_us (narrow: the weight of the narrow forms).
+struct StepCost {
+  double base, per_block, narrow;
+};
 struct FormQuery {
   int cus;  // compute units of the device
   int64_t heads, N, tiles;
   bool causal;
   double block_us;  // the tile contractions of one 16-row block at one CU's MFMA rate
-  double base, per_block;
+  StepCost step;
+  double merge_us;  // adding one more set's sums of one 16-row block at the end of a round
+  double margin = 1.0;  // by which another unsplit form has to be faster than the whole blocks
 };
 
 // Estimated time of a kernel's forms.  Equal (dense) blocks cost the rounds of
 // the fullest CU, causal ones the larger of the mean load and the heaviest
 // block's steps; a step has at least the four 16-row blocks that occupy every
-// SIMD, and kRound is a round's prologue, epilogue and merge of the sets.  The
-// constants (here, and the queries' base and per_block) were fitted to 37 shapes
-// (N = 256 to 32768, 1 to 48 heads, both types, every head dim) timed in every form:
-// the row kernels' choice is on average 1.2% slower than the best form (at most
-// 23%), the column kernels' 2% (18%).
+// SIMD, and kRound is a round's prologue and epilogue.  The constants (here, the
+// steps' costs, the merge's and the margins) were fitted to 1380 shapes (N = 64 to
+// 20000, 1 to 48 heads, both types, every head dim, dense and causal, grouped heads)
+// timed in every form.  On 460 others the choice is 1% (Pass 1, dQ) to 2% (forward,
+// dK and dV) slower than the best form, and over 2% slower than the whole blocks at
+// 1.4% of them, mostly calls of about 10 us.
 // Measured, whole blocks -> chosen form (us), row kernels: bf16 B1 H1 N8192 d64
 // causal forward 136 -> 34, Pass 1 206 -> 100; B1 H4 N4096 d128 dense 105 -> 48, 229
 // -> 152; B2 H4 N777 d128 26 -> 13, 55 -> 33; fp32 B1 H1 N256 d64 14 -> 7, 46 -> 27.
@@ -94,7 +100,8 @@ inline int pick_form(const FormQuery& q, std::initializer_list<Form> forms, Form
     const int64_t shares = (int64_t)f.sets * f.parts;
     const double share = (double)((q.tiles + shares - 1) / shares);
     auto step = [&](int64_t workgroups) {
-      return q.block_us * (q.base + q.per_block * f.weight * std::max<int64_t>(4, workgroups * f.blocks * f.sets));
+      const int64_t blocks = std::max<int64_t>(4, workgroups * f.blocks * f.sets);
+      return q.block_us * (q.step.base + q.step.per_block * f.weight * (double)blocks);
     };
     const int64_t k = (total + q.cus - 1) / q.cus;  // workgroups of the fullest CU
     double t;
@@ -105,10 +112,10 @@ inline int pick_form(const FormQuery& q, std::initializer_list<Form> forms, Form
     } else {
       t = share * ((double)(k / f.resident) * step(f.resident) + (k % f.resident != 0 ? step(k % f.resident) : 0));
     }
-    t += kRound * (double)((k + f.resident - 1) / f.resident);
-    // equal blocks are split only for a clear gain: an estimated gain of a few percent
-    // was a loss (fp32 B1 H12 Hkv6 N5050 d64 Pass 2: 2481 us split, 2434 unsplit)
-    if (!q.causal && f.parts > 1) t *= 1.08;
+    t += (kRound + q.merge_us * f.blocks * (f.sets - 1)) * (double)((k + f.resident - 1) / f.resident);
+    // splits cost what the estimate does not see (streams of several heads in flight,
+    // the reduction's launch): they have to be clearly faster
+    if (i > 0) t *= f.parts > 1 ? 1.08 : q.margin;
     t += f.extra_us;
     if (i == 0 || t < least) {
       best = i;

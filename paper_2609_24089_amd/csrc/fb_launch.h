@@ -167,6 +167,25 @@ template <auto kKernel> int causal_resident(const Problem& p, const Grid& g, int
   return p.causal == 0 ? 0 : balanced_order(g.total, resident_blocks<kKernel>(threads), device_cus());
 }
 
+// What a step of each kernel costs: base, per 16-row block, and what a block of the
+// narrow forms weighs (csrc/fb_forms.h; the figures' origin is beside pick_form()).
+template <typename T> constexpr bool kBf = sizeof(T) == 2;
+template <typename T> constexpr StepCost kFwdStep = kBf<T> ? StepCost{7.0, 0.36, 2.1} : StepCost{5.0, 1.2, 1.0};
+template <typename T> constexpr StepCost kRowsStep = kBf<T> ? StepCost{4.6, 0.62, 1.2} : StepCost{2.8, 1.2, 1.1};
+template <typename T> constexpr StepCost kP1Step = kBf<T> ? StepCost{7.7, 0.38, 1.55} : StepCost{4.5, 0.45, 1.0};
+template <typename T> constexpr StepCost kColsStep = kBf<T> ? StepCost{8.6, 0.48, 1.8} : StepCost{3.3, 0.39, 1.6};
+template <typename T> constexpr StepCost kP2Step = kBf<T> ? StepCost{7.2, 0.48, 1.55} : StepCost{5.3, 0.38, 1.0};
+// Row kernels leave their whole blocks only for an estimated gain of a tenth.
+constexpr double kRowMargin = 1.1;
+// The wave pairs of Pass 2 at bf16 d = 256 (two waves per SIMD) against the one-wave
+// form that its splits run.
+constexpr double kPairWeight = 0.2;
+
+// Adding one more wave set's `sums` accumulators of one 16-row block through LDS: 1.5 us
+// per 64 KB where a block's sums are large; with narrower heads it does not show
+// beside the rest of a round.
+inline double merge_us(int sums, int64_t d) { return d < 256 ? 0.0 : 1.5 * sums * (double)d / 1024; }
+
 // Time of `contractions` tile contractions of one 16-row block, in us at 85% of the
 // rate that a large matrix product reached on one CU (1366 TFLOP/s bf16, 154 fp32,
 // on 256 CUs).
@@ -197,7 +216,8 @@ template <typename T, int D> constexpr SetShape set_shape(int nw, int tensors, i
 }
 // Whether blocks of nw waves are worth building beside those of twice as many, the
 // next wider form: not where those have the same sets and need no more than a CU's four
-// SIMDs, so that a step takes them as long and they hold twice the rows.
+// SIMDs, so that a step takes them as long and they hold twice the rows (a gain of half
+// a merge, under 0.5 us, on problems of one such block a head).
 constexpr bool worth_building(SetShape s, SetShape twice) { return s.ks != twice.ks || 2 * s.nw * s.ks > 4; }
 
 // ---------------------------------------------------------------------------
@@ -344,9 +364,8 @@ template <typename T, int D, int NW> struct Pass2Small {
                         const float* E, void* Kt, void* Vt, hipStream_t s);
 };
 template <typename T, int D, int NW> Form ColsSmall<T, D, NW>::form() {
-  // 16 rows per wave with K in registers read an LDS operand per bf16 MFMA, the
-  // whole shape about 0.6
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks, 1, 0.0, sizeof(T) == 2 ? 1.6 : 1.0};
+  constexpr int kThreads = 64 * NW * kS.ks;
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(kThreads), kThreads, 1, 0.0, kColsStep<T>.narrow};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -364,7 +383,8 @@ int32_t ColsSmall<T, D, NW>::launch(const Problem& p, const void* Q, const void*
   return BOB_EUNSUPPORTED;
 }
 template <typename T, int D, int NW> Form Pass2Small<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  constexpr int kThreads = 64 * NW * kS.ks;
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(kThreads), kThreads, 1, 0.0, kP2Step<T>.narrow};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -427,13 +447,14 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
         whole.sets = 2;
       else if constexpr (!kSection)
         whole.resident = columns_resident<T, D, kPass2, false>(false);
-      // the wide blocks that an unsplit dense Pass 2 runs in (below) take 0.94-0.97 of
-      // the narrow ones' time, so a split has that much more to gain (bf16 B1 H12 Hkv6
-      // N10099 d128: unsplit 2254 us, four parts 2482; B1 H16 Hkv8 N6000: two parts 1084)
+      // what an unsplit Pass 2 runs in (below): wide blocks, wave pairs
       if constexpr (!kSection && kPass2 && Cfg<T, D>::kP2W.mr > 0)
         if (constexpr Shape w = Cfg<T, D>::kP2W; !two && o.wave_sets == 0 && !p.causal && o.flush_tiles <= 0 &&
             grid_for(p, 16 * w.mr * w.nw, true).total >= cus)
-          whole = {w.mr * w.nw, 1, 1, 64 * w.nw, 1, 0.0, 0.92};
+          whole = {w.mr * w.nw, 1, 1, 64 * w.nw};
+      if constexpr (!kSection && kPass2 && Cfg<T, D>::kP2P.mr > 0)
+        if (constexpr Shape q = Cfg<T, D>::kP2P; o.wave_sets == 0 && o.flush_tiles <= 0)
+          whole = {q.nw / 2, 1, 1, 64 * q.nw, 1, 0.0, kPairWeight};
       // narrow blocks: on grids with no more whole blocks than CUs, where wave
       // sets may be chosen and the whole block does not run in wave pairs
       if constexpr (!kSection && !(kPass2 && Cfg<T, D>::kP2P.mr > 0))
@@ -449,8 +470,8 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
           split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), 64 * s.nw, n,
                       4.0 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};
       const int form = pick_form(
-          {cus, p.B * p.Hkv, p.N, iters, p.causal != 0, block_us<T>(kPass2 ? 8 : 4, p.d), kPass2 ? 6.0 : 8.0,
-           kPass2 ? 1.2 : 0.8},
+          {cus, p.B * p.Hkv, p.N, iters, p.causal != 0, block_us<T>(kPass2 ? 8 : 4, p.d),
+           kPass2 ? kP2Step<T> : kColsStep<T>, merge_us(2, p.d)},
           {whole, n4, n2, n1, split[2], split[3], split[4], split[5], split[6], split[7], split[8]});
       if (form >= 4) c.parts = form - 2;
       else if (form >= 1) narrow = 8 >> form;
@@ -506,8 +527,9 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
 }
 
 // The query of a row kernel's launch.
-template <typename T> FormQuery row_query(const Problem& p, int contractions) {
-  return {device_cus(), p.B * p.H, p.N, (p.N + kBS - 1) / kBS, p.causal != 0, block_us<T>(contractions, p.d), 4.5, 0.45};
+template <typename T> FormQuery row_query(const Problem& p, int contractions, int sums, const StepCost& step) {
+  return {device_cus(), p.B * p.H, p.N, (p.N + kBS - 1) / kBS, p.causal != 0, block_us<T>(contractions, p.d), step,
+          merge_us(sums, p.d), kRowMargin};
 }
 
 template <typename T, int D, int NW> struct FwdSmall {
@@ -522,7 +544,8 @@ template <typename T, int D, int NW> struct FwdSmall {
                         hipStream_t s);
 };
 template <typename T, int D, int NW> Form FwdSmall<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  constexpr int kThreads = 64 * NW * kS.ks;
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(kThreads), kThreads, 1, 0.0, kFwdStep<T>.narrow};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -616,7 +639,8 @@ template <typename T, int D, int NW> struct RowsSmall {
                         const float* L, void* dQ, float* Dv, hipStream_t s);
 };
 template <typename T, int D, int NW> Form RowsSmall<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  constexpr int kThreads = 64 * NW * kS.ks;
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(kThreads), kThreads, 1, 0.0, kRowsStep<T>.narrow};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -649,7 +673,8 @@ template <typename T, int D, int NW> struct Pass1Small {
                         const void* dQ, void* Qt, void* dOt, float* alpha, float* E, hipStream_t s);
 };
 template <typename T, int D, int NW> Form Pass1Small<T, D, NW>::form() {
-  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(64 * NW * kS.ks), 64 * NW * kS.ks};
+  constexpr int kThreads = 64 * NW * kS.ks;
+  if constexpr (kBuilt) return {NW, kS.ks, resident_blocks<kernel()>(kThreads), kThreads, 1, 0.0, kP1Step<T>.narrow};
   else return {};
 }
 template <typename T, int D, int NW>
@@ -688,21 +713,21 @@ FB_PASS1_SMALL(extern, bf16, 128)
 template <typename T, int D> int fwd_form(const Problem& p, Form* chosen = nullptr) {
   constexpr Shape c = Cfg<T, D>::kFwd;
   constexpr auto whole = &attn_fwd_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
-  return pick_form(row_query<T>(p, 2),
+  return pick_form(row_query<T>(p, 2, 1, kFwdStep<T>),
                    {{c.mr * c.nw, 1, resident_blocks<whole>(64 * c.nw), 64 * c.nw}, FwdSmall<T, D, 4>::form(),
                     FwdSmall<T, D, 2>::form(), FwdSmall<T, D, 1>::form(), FwdWide<T, D>::form()}, chosen);
 }
 template <typename T, int D> int bwd_rows_form(const Problem& p, Form* chosen = nullptr) {
   constexpr Shape c = Cfg<T, D>::kRows;
   constexpr auto whole = &attn_bwd_rows_kernel<T, D, c.mr, c.nw, c.occ, c.st>;
-  return pick_form(row_query<T>(p, 3),
+  return pick_form(row_query<T>(p, 3, 1, kRowsStep<T>),
                    {{c.mr * c.nw, 1, resident_blocks<whole>(64 * c.nw), 64 * c.nw}, RowsSmall<T, D, 4>::form(),
                     RowsSmall<T, D, 2>::form(), RowsSmall<T, D, 1>::form(), RowsWide<T, D>::form()}, chosen);
 }
 template <typename T, int D> int pass1_form(const Problem& p, Form* chosen) {  // the dQ form
   constexpr Shape c = Cfg<T, D>::kP1;
   constexpr auto whole = &bob_pass1_kernel<T, D, c.mr, c.nw, c.occ, c.st, kWithDQ, c.ds, c.pf>;
-  return pick_form(row_query<T>(p, 10),
+  return pick_form(row_query<T>(p, 10, 3, kP1Step<T>),
                    {{c.mr * c.nw, 1, resident_blocks<whole>(64 * c.nw), 64 * c.nw}, Pass1Small<T, D, 4>::form(),
                     Pass1Small<T, D, 2>::form(), Pass1Small<T, D, 1>::form()}, chosen);
 }

@@ -42,7 +42,8 @@ class Form(ctypes.Structure):
 class Query(ctypes.Structure):
     _fields_ = [("cus", ctypes.c_int), ("heads", ctypes.c_int64), ("N", ctypes.c_int64), ("tiles", ctypes.c_int64),
                 ("causal", ctypes.c_bool), ("block_us", ctypes.c_double), ("base", ctypes.c_double),
-                ("per_block", ctypes.c_double)]
+                ("per_block", ctypes.c_double), ("narrow", ctypes.c_double), ("merge_us", ctypes.c_double),
+                ("margin", ctypes.c_double)]
 
 
 @pytest.fixture(scope="module")
@@ -60,8 +61,8 @@ def forms(tmp_path_factory):
     return lib
 
 
-def pick(lib, cus, heads, N, forms, causal=False):
-    q = Query(cus, heads, N, (N + 31) // 32, causal, 0.1, 4.5, 0.45)
+def pick(lib, cus, heads, N, forms, causal=False, merge_us=0.0, margin=1.0):
+    q = Query(cus, heads, N, (N + 31) // 32, causal, 0.1, 4.5, 0.45, 1.0, merge_us, margin)
     return lib.pick(ctypes.byref(q), len(forms), (Form * len(forms))(*forms))
 
 
@@ -117,3 +118,15 @@ def test_narrower_blocks_with_the_same_sets_are_never_taken(forms):
         assert pick(forms, 256, heads, N, [whole, Form(2, 1, 1), Form(1, 1, 1)], causal) == 0
         assert pick(forms, 256, heads, N, [Form(8, 1, 2), Form(4, 2, 2), Form(2, 4, 1), Form(1, 4, 1), Form(8, 2, 1)],
                     causal) != 4
+
+
+def test_whole_blocks_stay_where_little_is_gained(forms):
+    """Two forms of equal estimate but for what the query adds: the merge of the sets,
+    the margin of the row kernels, the splits' own margin and cost."""
+    f = [Form(4, 1, 1), Form(4, 2, 1)]
+    assert pick(forms, 256, 64, 256, f) == 1                        # half the steps
+    assert pick(forms, 256, 64, 256, f, margin=4.0) == 0
+    assert pick(forms, 256, 64, 256, f, merge_us=2.0) == 0          # 8 us to merge four blocks
+    assert pick(forms, 256, 64, 256, [Form(4, 1, 1), Form(4, 1, 1, parts=2, extra_us=0.5)]) == 0   # a second round of 4 us
+    assert pick(forms, 256, 16, 8192, [Form(8, 1, 1), Form(8, 1, 1, parts=2, extra_us=9.0)]) == 0  # 1024 blocks fill it
+    assert pick(forms, 256, 1, 8192, [Form(8, 1, 1), Form(8, 1, 1, parts=2, extra_us=9.0)]) == 1   # 64 blocks do not

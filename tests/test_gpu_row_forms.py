@@ -47,8 +47,8 @@ def problem(kernel, dt, d, form, causal, least, group=1):
     """(H, N) of the least work, N >= least, that runs `form`."""
     fb = lib()
     found = []
-    for N in (70, 149, 200, 301, 523, 777, 1101, 2100, 4099):
-        for Hkv in (1, 2, 3, 5, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768):
+    for N in (70, 101, 149, 200, 250, 301, 401, 523, 650, 777, 1101, 1500, 2100, 3001, 4099):
+        for Hkv in (1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 512, 768):
             if N >= least and fb.row_layout(kernel, DT[dt], 1, Hkv * group, Hkv, N, d, causal) == form:
                 found.append((Hkv * group * N * N, Hkv * group, N))
     assert found, "no problem runs this form"
