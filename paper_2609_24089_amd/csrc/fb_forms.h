@@ -66,9 +66,9 @@ struct FormQuery {
 // SIMD, and kRound is a round's prologue and epilogue.  The constants (here, the
 // steps' costs, the merge's and the margins) were fitted to 1380 shapes (N = 64 to
 // 20000, 1 to 48 heads, both types, every head dim, dense and causal, grouped heads)
-// timed in every form.  On 460 others the choice is 1% (Pass 1, dQ) to 2% (forward,
-// dK and dV) slower than the best form, and over 2% slower than the whole blocks at
-// 1.4% of them, mostly calls of about 10 us.
+// timed in every form.  On 460 others the choice is 1% (Pass 1, dQ) to 2% (the rest)
+// slower than the best form, and over 2% slower than the whole blocks at 1% of them,
+// mostly calls of about 10 us.
 // Measured, whole blocks -> chosen form (us), row kernels: bf16 B1 H1 N8192 d64
 // causal forward 136 -> 34, Pass 1 206 -> 100; B1 H4 N4096 d128 dense 105 -> 48, 229
 // -> 152; B2 H4 N777 d128 26 -> 13, 55 -> 33; fp32 B1 H1 N256 d64 14 -> 7, 46 -> 27.

@@ -464,11 +464,12 @@ int32_t plan_columns(const Problem& p, const ColumnOpts& o, ColumnPlan* out) {
           n1 = narrow_form<T, D, kPass2, 1>();
         }
       // parts: 16 bytes an output element and part, written and read at 6 TB/s,
-      // and a launch; not where wave sets are asked for, which a split has none of
+      // and a launch (4 us in a trace, 6 with its gap); not where wave sets are asked
+      // for, which a split has none of
       if (o.parts == 0 && o.wave_sets == 0 && iters < kLongBlock && iters >= o.min_iters)
         for (int n = 2; n <= kMaxParts; ++n)
           split[n] = {s.mr * s.nw, 1, columns_resident<T, D, kPass2, kSection>(true), 64 * s.nw, n,
-                      4.0 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};
+                      6.2 + 16.0 * n * (double)(p.B * p.Hkv * p.N * p.d) / 6e6};
       const int form = pick_form(
           {cus, p.B * p.Hkv, p.N, iters, p.causal != 0, block_us<T>(kPass2 ? 8 : 4, p.d),
            kPass2 ? kP2Step<T> : kColsStep<T>, merge_us(2, p.d)},
