@@ -114,9 +114,10 @@ def test_split_on_a_side_stream(fb):
 def test_automatic_choice(fb):
     """Automatic parts split a causal grid up to about 8 jobs per CU (at most 8
     parts); Pass 2 splits a dense grid only when it has fewer workgroups than
-    CUs, the first backward to about 8 jobs per CU as well; blocks of fewer
-    than 1024 streamed iterations and the multi-head workloads stay
-    unsplit; the automatic result equals the forced one bit for bit."""
+    CUs, the first backward to about 8 jobs per CU as well; the multi-head
+    workloads stay unsplit, and so do the problems with blocks of fewer than
+    1024 streamed iterations below, which an estimate decides; the automatic
+    result equals the forced one bit for bit."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     N, d = 16384, 128
     grid = lambda Hkv: Hkv * (N // 64)          # bf16 d = 128 Pass 2: 64 key rows per workgroup
@@ -135,7 +136,7 @@ def test_automatic_choice(fb):
         pb = min(8, -(-8 * cus // (Hkv * (N // 128))))
         want_b = 0 if pb < 2 else pb * 2 * Hkv * N * d * 4
         assert ws_bytes(fb, False, fb.BOB_BF16, 1, 16, Hkv, N, d, causal) == want_b, (Hkv, causal)
-    # short blocks (fewer than 1024 streamed iterations) are never split
+    # short blocks (fewer than 1024 streamed iterations) that gain nothing from a split
     for Hkv, n in ((12, 4096), (12, 2048), (1, 500)):
         for causal in (0, 1):
             assert ws_bytes(fb, True, fb.BOB_BF16, 4, 12 if Hkv == 12 else 4, Hkv, n, 64, causal) == 0
